@@ -31,9 +31,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # the sources of the round kernel and of the host code that picks its shape:
 # counters taken on other text are stale
 KERNEL_SOURCES = ["paper_2607_05302_amd/csrc/kernel_round.hpp",
+                  "paper_2607_05302_amd/csrc/kernel_tile.hpp",
                   "paper_2607_05302_amd/csrc/common.hpp",
                   "paper_2607_05302_amd/csrc/radsort.hip"]
-ROUND_KERNEL = "k_round<"
+ROUND_KERNEL = "_round<"  # k_tile_round (the default draw order) or k_round
 COPY_KERNEL = "k_stream_copy"
 
 

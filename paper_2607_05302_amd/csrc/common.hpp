@@ -100,23 +100,32 @@ __device__ __forceinline__ X* blockat(X* A, X* T, uint32_t j, uint32_t two_sigma
 
 // --- prefix sums ------------------------------------------------------------------
 
-// inclusive scan across the 64 lanes of a wave
+// One step of a wave scan on the data-parallel-primitive path: adds the value that
+// the control word CTRL brings from a lower lane, in the rows of ROWS (0 elsewhere).
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+
+// inclusive scan across the 64 lanes of a wave (all of them active): within the rows
+// of 16 lanes by shifts of 1, 2, 4 and 8, then the last lane of a row added to the
+// next row (rows 1 and 3) and lane 31 to the upper half.  No LDS: the shuffles this
+// replaces cost six dependent LDS round trips.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        uint32_t u = __shfl_up(v, o, 64);
-        if (lane >= (uint32_t)o) v += u;
-    }
+    v = dpp_add<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);  // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast:15
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast:31
     return v;
 }
 
+// sum over the 64 lanes of a wave (all of them active), the same in every lane
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_scan(v), 63);
 }
 
 // Hand-off of global memory between the threads of one workgroup: every store a

@@ -17,6 +17,7 @@
 #include "common.hpp"
 #include "kernels_state.hpp"
 #include "kernel_round.hpp"
+#include "kernel_tile.hpp"
 #include "kernels_prefix.hpp"
 #include "kernels_small.hpp"
 #include "kernels_wg.hpp"
@@ -108,6 +109,32 @@ template <int KB> struct LargeTile {  // KB = 4: keys of 4 bytes; 8: keys of 8 b
 };
 constexpr uint64_t kLargeTileMin = 1ull << 28;  // elements
 
+// Tiles of k_tile_round (the default draw order, digits of at most 8 bits, blocks of
+// 1024 elements or more).  Two workgroups share a compute unit with either tile; the
+// large one holds 16384 slots (4-byte keys, records of at most 8 bytes) or 8192, so
+// that a digit's run in a tile is 64 or 32 elements long (256 bytes).  Time per round,
+// small tile against large one, uniform keys: uint32 pairs 32.0 / 35.3 us at 2^21, 46.6 /
+// 43.1 at 2^22, 105 / 95 at 2^24, 417 / 323 at 2^26; uint64 + uint32 27.5 / 26.7 us at
+// 2^20, 146 / 121 at 2^24, 708 / 498 at 2^26; uint64 keys 24.2 / 23.5 us at 2^20, 531 / 391 at
+// 2^26: hence tile_large_min.  At 2^28 uint32 pairs, b = 2048, the large tile takes
+// 1.240 ms per round (3.46 TB/s) against 1.536 ms for one workgroup per compute unit of
+// the same tile in k_round (2.80 TB/s).
+template <int KB, int VB, bool LARGE> struct TileShape {
+    static constexpr bool NARROW = KB == 4 && VB <= 4;
+    static constexpr int WAVES = 8;
+    static constexpr int ITEMS = (NARROW ? 16 : 8) << (LARGE ? 1 : 0);
+    using Shape = RoundShape<WAVES, ITEMS, false, true, 4>;
+    static constexpr int E = 64 * WAVES * ITEMS;
+};
+constexpr uint64_t tile_large_min(uint32_t kb, uint32_t vb)
+{
+    return kb == 4 && vb <= 4 ? 1ull << 22 : 1ull << 20;
+}
+template <bool LARGE> uint32_t tile_shape_elems(uint32_t kb, uint32_t vb)
+{
+    return kb == 4 && vb <= 4 ? TileShape<4, 4, LARGE>::E : TileShape<8, 8, LARGE>::E;
+}
+
 struct Geo {
     uint64_t n = 0;
     uint32_t kb = 0, vb = 0, bits = 0, sigma = 0, nt = 0, b = 0, log2b = 0;
@@ -120,6 +147,8 @@ struct Geo {
     bool fin_temps_pack = false;  // the same for a packed state (n_pi + sigma blocks)
     bool pack_ok = false;         // one-call sorts pack the last round (plan_round)
     bool large_tile = false;      // the Radsort round runs LargeTile (E = 16384)
+    bool tile = false;            // the Radsort round is k_tile_round
+    bool tile_large = false;      // ... with its large tile
 };
 
 // Workspace regions (byte offsets), each 256-byte aligned.
@@ -193,6 +222,13 @@ int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bit
                    ((key_bytes == 4 && payload_bytes <= 4) || (key_bytes == 8 && payload_bytes == 0));
     g.E = !g.large_tile ? tile_elems(g.kb, g.vb, g.bits, false)
           : key_bytes == 4 ? (uint32_t)LargeTile<4>::E : (uint32_t)LargeTile<8>::E;
+    const uint32_t seq_E = g.E;  // the tile of the sequential draw order
+    g.tile = digit_bits <= 8 && g.log2b >= kTileMinLog2b &&
+             !(opts && (opts->flags & RADSORT_F_SEQ_DRAWS));
+    if (g.tile) {
+        g.tile_large = n >= tile_large_min(g.kb, g.vb);
+        g.E = g.tile_large ? tile_shape_elems<true>(g.kb, g.vb) : tile_shape_elems<false>(g.kb, g.vb);
+    }
     g.oop_E = tile_elems(g.kb, g.vb, g.bits, true);
 #ifdef RS_DEBUG_ORDER
     if (opts && (opts->flags & RADSORT_F_DEBUG_ORDER) && g.b > g.E) return RADSORT_E_UNSUPPORTED;
@@ -201,10 +237,14 @@ int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bit
     uint64_t slots = (g.nb + g.sigma) << g.log2b;
     g.tiles = (uint32_t)((slots + g.E - 1) / g.E);
     // ring slots (a power of two): one per tile when the tiles fit, else the cap;
-    // with a slot per tile no slot is ever reused
+    // with a slot per tile no slot is ever reused.  The ring and the super-tiles are
+    // laid out for the smaller tile of the two draw orders, so that one workspace
+    // serves both.
+    const uint32_t lay_E = std::min(g.E, seq_E);
+    const uint32_t lay_tiles = (uint32_t)((slots + lay_E - 1) / lay_E);
     const uint32_t ring_cap = std::max<uint32_t>(256u, kRingWords / g.sigma);
     uint32_t ring_w = 32;
-    while (ring_w < g.tiles && ring_w < ring_cap) ring_w <<= 1;
+    while (ring_w < lay_tiles && ring_w < ring_cap) ring_w <<= 1;
     g.ring_w = ring_w;
     g.ring_log2 = ilog2(g.ring_w);
     // a super-tile spans at least 2^kSuperSlotsLog2 slots and at least one block
@@ -522,6 +562,20 @@ int launch_round_t(const Geo& g, TileArgs<KB, VB>& a, hipStream_t s, bool dyn = 
     using NS = typename N::Shape;
     const uint32_t tiles = OOP ? (uint32_t)((g.n + g.oop_E - 1) / g.oop_E) : g.tiles;
     if (tiles == 0) return RADSORT_OK;
+    if constexpr (!OOP) {
+        if (g.tile && !seq) {
+            using TL = TileShape<KB, VB, true>;
+            using TS = TileShape<KB, VB, false>;
+            const void* kern =
+                g.tile_large
+                    ? (g.bits == 8 ? (const void*)&k_tile_round<KB, VB, 8, typename TL::Shape>
+                                   : (const void*)&k_tile_round<KB, VB, 0, typename TL::Shape>)
+                    : (g.bits == 8 ? (const void*)&k_tile_round<KB, VB, 8, typename TS::Shape>
+                                   : (const void*)&k_tile_round<KB, VB, 0, typename TS::Shape>);
+            return launch_dynamic(kern, tiles, 64 * (g.tile_large ? TL::WAVES : TS::WAVES), a, s,
+                                  false);
+        }
+    }
     if constexpr (!OOP && ((KB == 4 && VB <= 4) || (KB == 8 && VB == 0))) {
         if (g.large_tile) {  // 8-bit or narrower digits only (make_geo); a workgroup per tile
             using LS = typename LargeTile<KB>::Shape;

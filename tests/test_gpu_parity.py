@@ -365,3 +365,66 @@ def test_shared_launch_forms_at_scale(kb):
         fn(dk, dv, check=True, shared=True)
         assert np.array_equal(from_dev(dk, kb).astype(np.uint64), ok), fn.__name__
         assert np.array_equal(from_dev(dv, 4).astype(np.uint64), ov), fn.__name__
+
+
+# ---------------------------------------------------------------- the round's tiles
+
+# The large tile of the default draw order (from 2^22 records of at most 8 bytes with
+# 4-byte keys, 2^20 of the others) at the edges of its range: one element below, at and
+# above the threshold, a whole number of tiles, a ragged last tile, blocks of exactly 1024
+# elements, of one tile and larger than a tile, narrow digits, and digits spread or
+# skewed within a wave (ranks by OR table or by ballots).
+TILE_EDGE = [
+    ("uniform", (1 << 22) - 1, 4, 4, 8, 1024),
+    ("uniform", (1 << 22) + 1, 4, 4, 8, 1024),
+    ("zipf", 1 << 22, 4, 4, 8, 2048),
+    ("uniform", (1 << 22) + 16383, 4, 0, 8, 16384),
+    ("few", (1 << 22) + 5, 4, 4, 8, 65536),
+    ("low20", (1 << 22) + 4097, 4, 4, 4, 1024),
+    ("uniform", (1 << 20) - 1, 8, 0, 8, 1024),
+    ("zipf", (1 << 20) + 8191, 8, 0, 8, 8192),
+    ("uniform", (1 << 20) + 1, 8, 4, 8, 1024),
+    ("sorted", (1 << 20) + 77, 8, 8, 8, 2048),
+    ("equal", (1 << 20) + 1023, 4, 8, 8, 1024),
+    ("zipf", (1 << 20) + 8193, 4, 8, 5, 65536),
+]
+
+
+@pytest.mark.parametrize("case", TILE_EDGE, ids=lambda c: "-".join(map(str, c)))
+def test_tile_edges_match_oracle(case):
+    """Every round's P, f and logical contents, and the finalized arrays, both through
+    the step interface; then the one-call sort of the same input."""
+    dist, n, kb, vb, bits, b = case
+    say(f"tile edges {case}")
+    keys, vals = inputs(dist, n, kb, vb, seed=7)
+    sigma, nt = oracle.digit_params(kb, bits)
+    dk, dv = to_dev(keys), to_dev(vals) if vb else None
+    st = radsort.State(dk, dv, digit_bits=bits, block_elems=b)
+    R = oracle.Radsort(keys, vals, sigma, nt, b)
+    st.setup()
+    R.setup()
+    for r in range(min(nt, 3)):
+        st.round()
+        R.round(nt - 1 - r)
+        _, pidx, plen, f = st.read()
+        oidx, olen = R.P()
+        assert f == R.f
+        assert np.array_equal(pidx.astype(np.uint64), oidx)
+        assert np.array_equal(plen.astype(np.uint64), olen)
+        lk, lv = st.logical()
+        ok, ov, _ = R.logical()
+        assert np.array_equal(from_dev(lk, kb).astype(np.uint64), ok), f"round {r}"
+        if vb:
+            assert np.array_equal(from_dev(lv, vb).astype(np.uint64), ov), f"round {r}"
+    for _ in range(nt - min(nt, 3)):
+        st.round()
+    st.finalize()
+    st.read()
+    ek, ev = oracle.radsort(keys, vals, sigma, nt, b)
+    sk, sv = to_dev(keys), to_dev(vals) if vb else None
+    radsort.sort_(sk, sv, digit_bits=bits, block_elems=b, check=True)
+    for gk, gv in ((dk, dv), (sk, sv)):
+        assert np.array_equal(from_dev(gk, kb).astype(np.uint64), ek)
+        if vb:
+            assert np.array_equal(from_dev(gv, vb).astype(np.uint64), ev)
+    st.close()
