@@ -96,7 +96,8 @@ struct TileArgs {
     uint64_t n;              // out-of-place only
     uint32_t* agg;           // tile counts [2^ring_log2][sigma], zeroed per round
     uint32_t* done;          // [2^ring_log2]: tile + 1 once done, zeroed per round
-    const uint32_t* stbase;  // [super-tile][sigma]: digit counts before each super-tile
+    const uint32_t* stbase;  // [super-tile][sigma]: digit counts before each super-tile,
+    const uint32_t* stsum;   // from the start of its chunk: [chunk][sigma], the rest
     uint32_t* err;
     uint32_t* tile_ctr;      // dynamic launches: next tile to claim, zero on entry
     uint32_t shift, bits, log2b, npi, ring_log2;
@@ -111,10 +112,21 @@ struct TileArgs {
     // the input blocks in logical order, which keeps every draw behind the blocks
     // already read although the offsets make buckets draw up to sigma blocks early.
     const uint32_t* pack_est;
+    const uint32_t* mode;    // this round's mode, decided on the device (RoundModes), or null:
+                             // packed when pack_est is given
     K* Xk;
     V* Xv;
     uint32_t npi_x;          // physical blocks a draw can name: npi, + sigma when packed
 };
+
+// elements with digit d before super-tile u (kernels_prefix.hpp)
+constexpr uint32_t kScanRows = 64;  // super-tiles per chunk
+template <int KB, int VB>
+__device__ __forceinline__ uint32_t super_start(const TileArgs<KB, VB>& a, uint32_t u,
+                                                uint32_t sigma, uint32_t d)
+{
+    return a.stbase[(uint64_t)u * sigma + d] + a.stsum[(uint64_t)(u / kScanRows) * sigma + d];
+}
 
 // Timeline builds (RS_TIMELINE defined): thread 0 of each workgroup records the
 // 100 MHz real-time counter at the phase boundaries of every tile, so that a
@@ -468,7 +480,7 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_round(TileArgs<KB, VB> a)
                 wh[w * SMAX + d] = run;
                 run += c;
             }
-            st_agent(mycnt + d, run | epoch_bit(tile, wlog));
+            if (mst > 1) st_agent(mycnt + d, run | epoch_bit(tile, wlog));
             cnt[d] = run;
         }
         const uint32_t incl = wave_incl_scan(run);
@@ -497,7 +509,7 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_round(TileArgs<KB, VB> a)
                 wh[w * SMAX + d] = run;
                 run += c;
             }
-            st_agent(mycnt + d, run | epoch_bit(tile, wlog));
+            if (mst > 1) st_agent(mycnt + d, run | epoch_bit(tile, wlog));
             cnt[d] = run;
             excl[d] = run;
         }
@@ -546,7 +558,7 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_round(TileArgs<KB, VB> a)
     // ---- look back over the super-tile -----------------------------------------------
     for (uint32_t d = tid; d < sigma; d += NT) {
         // the super-tile's digit start, requested with the first look-back loads
-        const uint32_t sbase = a.stbase[(uint64_t)(tile >> a.st_log2) * sigma + d];
+        const uint32_t sbase = super_start(a, tile >> a.st_log2, sigma, d);
         // sum the counts of tiles st0 .. tile-1, up to kLookbackWin loads at once;
         // while one has not published, poll that one alone
         uint32_t acc = 0, k = tile, spins = 0;

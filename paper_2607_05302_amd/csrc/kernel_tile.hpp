@@ -19,6 +19,7 @@
 
 #include "common.hpp"
 #include "kernel_round.hpp"
+#include "kernels_state.hpp"
 
 namespace rs {
 
@@ -87,6 +88,13 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     const uint64_t wmask = (1ull << wlog) - 1;
     const uint32_t mst = 1u << a.st_log2;  // tiles per super-tile
 
+    bool packed = a.pack_est != nullptr;
+    if (a.mode) {
+        const uint32_t m = *a.mode;
+        if (m == kModeSkip) return;  // the round's digit is the same for every element
+        packed = m == kModePacked;
+    }
+
     // ---- claim a tile; its blocks ----------------------------------------------------
     if (tid == 0) claimed = add_agent(a.tile_ctr, 1u);
     // f is clamped so that a corrupt state can never index past pi
@@ -154,8 +162,8 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     uint32_t Sd = 0, sbase = 0, poff = 0;
     if (d < sigma) {
         Sd = a.S[d];
-        sbase = a.stbase[(uint64_t)(tile >> a.st_log2) * sigma + d];
-        if (a.pack_est) poff = a.pack_est[d] & (b - 1);  // the packed round's offset
+        sbase = super_start(a, tile >> a.st_log2, sigma, d);
+        if (packed) poff = a.pack_est[d] & (b - 1);  // the packed round's offset
     }
     // reuse of this tile's ring slot: the done words of the tiles that must have
     // finished, requested now and checked before the counts are published
@@ -291,7 +299,8 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        st_agent(a.agg + (uint64_t)(tile & wmask) * sigma + d, c | epoch_bit(tile, wlog));
+        if (mst > 1)  // a super-tile of one tile has no look-back
+            st_agent(a.agg + (uint64_t)(tile & wmask) * sigma + d, c | epoch_bit(tile, wlog));
     }
     const uint32_t cincl = wave_incl_scan(c);
     if (lane == 63 && wave < DW) tmp[wave] = cincl;
@@ -402,7 +411,6 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     // whose input blocks they are.  Draw k of the round takes pool entry k: the input
     // block sigma + k (logical), or in the packed round the extra block npi + k for
     // k < sigma and then the input block k.
-    const bool packed = a.pack_est != nullptr;
     auto pool_entry = [&](uint32_t k) -> uint32_t {
         if (packed) return k < sigma ? a.npi + k : (k < a.npi ? a.pi_old[k] : a.npi_x);
         const uint32_t h = sigma + k;

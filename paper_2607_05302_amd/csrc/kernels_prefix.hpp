@@ -10,24 +10,83 @@
 #pragma once
 
 #include "common.hpp"
+#include "kernel_round.hpp"
 #include "kernels_state.hpp"
 
 namespace rs {
 
-constexpr int kHistCopies = 8192;  // LDS words of per-wave digit counts per workgroup
-constexpr int kScanRows = 64;      // super-tiles per chunk of the column scan
+constexpr uint32_t kHistLog2 = 12;  // LDS words of digit counts per workgroup: 4096
+constexpr int kHistWords = 1 << kHistLog2;
+constexpr uint32_t kCopiesLog2 = 4;  // at most 16 copies of each count
 constexpr int kMaxSuperBlocks = 2048;  // blocks of one super-tile held in LDS
 
-// cnt[u * sigma + d] = elements of super-tile u with digit d (for every u of the
-// grid; super-tiles past the input write zeros), and csum[c * sigma + d] += the
-// same for chunk c = floor(u / kScanRows) (csum zero on entry).  A super-tile
-// spans at most kMaxSuperBlocks blocks.
+// Exclusive sums down the columns of a[rows][sigma], in place, by one workgroup; the
+// column totals go to total[sigma].  The rows come from other workgroups and the results go to others: agent-scope accesses.
+// Several threads share a column, each a run of rows held in registers where it fits (32
+// rows), so that their loads, one trip to memory, are in flight together.  part: LDS,
+// max(NT, sigma) words.  Contains barriers.
+template <int NT>
+__device__ void scan_columns(uint32_t* a, uint32_t rows, uint32_t sigma, uint32_t* part,
+                             uint32_t* total)
+{
+    constexpr uint32_t REG = 32;
+    const uint32_t NP = sigma >= NT ? 1u : NT / sigma;  // threads per column
+    const uint32_t per = (rows + NP - 1) / NP;
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t i0 = 0; i0 < NP * sigma; i0 += NT) {
+        const uint32_t i = i0 + tid, d = i % sigma, q0 = min(rows, (i / sigma) * per),
+                       q1 = min(rows, q0 + per);
+        const bool mine = i < NP * sigma;
+        uint32_t x[REG], s = 0;
+        for (uint32_t q = q0; mine && q < q1; q += REG) {
+#pragma unroll
+            for (uint32_t k = 0; k < REG; k++)
+                x[k] = q + k < q1 ? ld_agent(a + (uint64_t)(q + k) * sigma + d) : 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < REG; k++) s += x[k];
+        }
+        __syncthreads();  // part is free
+        if (mine) part[i] = s;
+        __syncthreads();
+        uint32_t run = 0;
+        for (uint32_t k = d + i0; mine && k < i; k += sigma) run += part[k];
+        for (uint32_t q = q0; mine && q < q1; q += REG) {
+            if (per > REG) {
+#pragma unroll
+                for (uint32_t k = 0; k < REG; k++)
+                    x[k] = q + k < q1 ? ld_agent(a + (uint64_t)(q + k) * sigma + d) : 0u;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < REG; k++) {
+                if (q + k < q1) st_agent(a + (uint64_t)(q + k) * sigma + d, run);
+                run += x[k];
+            }
+        }
+        if (mine && i / sigma == NP - 1) {
+            // a run past the end of the rows has added up everything before it
+            st_agent(total + d, run);
+        }
+    }
+}
+
+// cnt[u * sigma + d] = elements with digit d in the super-tiles of u's chunk (kScanRows
+// rows) before u, for every u of the grid (super-tiles past the input count as empty),
+// and csum[c * sigma + d] = the same before chunk c, so that the digit start of
+// super-tile u is cnt[u][d] + csum[u / kScanRows][d].  A workgroup counts one super-tile;
+// the last one of a chunk to finish (counted in csum[c][0], zero on entry) scans the
+// chunk's rows, and the last chunk (counter *done, zero on entry) scans the chunks and
+// makes the round's plan from the digit totals, which also go to the last row, past the
+// input (plan: 1; 2: with element starts; 3: packed, see plan_round).  One launch: a scan
+// kernel of its own took 9 us at 2^24 elements and 12 us at 2^28.
 //
-// With plan != 0 (a grid of at most kScanRows workgroups: one chunk) no csum is
-// kept: the last workgroup to finish, found by the counter *done (zero on
-// entry), runs the column scan of k_column_scan itself and then the round's
-// plan (plan == 2: with element starts; 3: packed, see plan_round), so that no
-// scan kernel is needed.
+// The counting is bound by the read of the keys.  Counts are kept in `copies` LDS tables
+// laid out counter by counter (counter d of copy c at word d * copies + c), lane l adding
+// to copy l mod copies: equal digits of a wave then meet in different words and banks.
+// Measured per pass: 2^27 uint64 keys of 4096 skewed values 469 us with a table per wave,
+// 246 us with 16 copies by lane (4.4 TB/s); 2^28 uniform uint64 keys 430 and 444 us; 4, 16
+// and 32 copies are alike.
+//
+// A super-tile spans at most kMaxSuperBlocks blocks.
 template <int KB, bool OOP, int NT>
 __global__ __launch_bounds__(NT) void k_supertile_counts(
     const typename UInt<KB>::T* __restrict__ Ak, const typename UInt<KB>::T* __restrict__ Tk,
@@ -35,27 +94,62 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
     const uint32_t* __restrict__ f_in_p, uint64_t n, uint32_t shift, uint32_t bits,
     uint32_t log2b, uint32_t npi, uint32_t sts_log2, uint32_t* __restrict__ cnt,
     uint32_t* __restrict__ csum, uint32_t* err, uint32_t* __restrict__ done, uint32_t plan,
-    PlanPtrs pp)
+    PlanPtrs pp, RoundModes rm)
 {
     using K = typename UInt<KB>::T;
-    constexpr int NW = NT / 64;
+    constexpr uint32_t NW = NT / 64;
     constexpr int U = 16;  // loads in flight per thread
-    __shared__ uint32_t h[kHistCopies];
+    __shared__ uint32_t h[kHistWords];
     __shared__ uint32_t bphys[OOP ? 1 : kMaxSuperBlocks], blen_s[OOP ? 1 : kMaxSuperBlocks];
+    __shared__ uint32_t last, mode_s;
+    __shared__ uint64_t vary_s;
     const uint32_t sigma = 1u << bits, dmask = sigma - 1, two_sigma = 2 * sigma;
-    const uint32_t copies = max(1u, min<uint32_t>(NW, kHistCopies / sigma));
-    const uint32_t tid = threadIdx.x, wave = tid >> 6;
-    uint32_t* mine = h + (wave % copies) * sigma;
+    const uint32_t clog = min(kCopiesLog2, kHistLog2 - bits), copies = 1u << clog;
+    const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    uint32_t mode = plan == 3 ? kModePacked : kModeRun;
+    if (rm.vary && rm.r) {  // round 0 decides once its keys are read
+        mode = round_mode(*rm.vary, rm.r, rm.nt, bits);
+        if (mode == kModeSkip) {
+            if (blockIdx.x == 0 && tid == 0) rm.mode[rm.r] = mode;
+            return;
+        }
+    }
+    uint32_t* const mine = h + (lane & (copies - 1));
     for (uint32_t i = tid; i < copies * sigma; i += NT) h[i] = 0;
+    if (tid == 0) vary_s = 0;
 
     const uint64_t s0 = (uint64_t)blockIdx.x << sts_log2, span = 1ull << sts_log2;
     const uint32_t b = 1u << log2b;
-    uint64_t s1;
+    const K ref = rm.vary && !rm.r ? Ak[0] : (K)0;
+    K diff = 0;  // bits in which this thread's keys differ from the array's first
+    auto add = [&](K x) {
+        atomicAdd(mine + (((uint32_t)(x >> shift) & dmask) << clog), 1u);
+        diff |= x ^ ref;
+    };
     if constexpr (OOP) {
-        s1 = min<uint64_t>(n, s0 + span);
+        __syncthreads();
+        const uint64_t s1 = min<uint64_t>(n, s0 + span);
+        for (uint64_t c = s0; c < s1; c += (uint64_t)NT * U) {
+            K x[U];
+            if (c + (uint64_t)NT * U <= s1) {  // no checks
+#pragma unroll
+                for (int j = 0; j < U; j++) x[j] = Ak[c + j * NT + tid];
+#pragma unroll
+                for (int j = 0; j < U; j++) add(x[j]);
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < U; j++) {
+                const uint64_t sl = c + (uint64_t)j * NT + tid;
+                x[j] = sl < s1 ? Ak[sl] : (K)0;
+            }
+#pragma unroll
+            for (int j = 0; j < U; j++)
+                if (c + (uint64_t)j * NT + tid < s1) add(x[j]);
+        }
     } else {
         const uint32_t f_in = max(sigma, min(*f_in_p, npi));
-        const uint32_t nblk = (uint32_t)(span >> log2b);
+        const uint32_t nblk = max(1u, (uint32_t)(span >> log2b));
         const uint32_t L0 = sigma + (uint32_t)(s0 >> log2b);
         for (uint32_t i = tid; i < nblk; i += NT) {
             const uint32_t L = L0 + i;
@@ -72,117 +166,82 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
             bphys[i] = phys;
             blen_s[i] = len;
         }
-        s1 = s0 + span;
-    }
-    __syncthreads();
-    if constexpr (OOP) {
-        for (uint64_t c = s0; c < s1; c += (uint64_t)NT * U) {
+        __syncthreads();
+        // each wave reads pieces of a block, at most U * 64 slots long
+        const uint32_t plog = min<uint32_t>(log2b, 6 + 4);
+        static_assert(U == 16, "pieces of 1024 slots");
+        const uint32_t pieces = (uint32_t)(span >> plog);
+        const uint32_t first = (uint32_t)s0 & (b - 1);  // 0 unless a block spans super-tiles
+        for (uint32_t i = wave; i < pieces; i += NW) {
+            const uint32_t at = first + (i << plog), bi = at >> log2b, o0 = at & (b - 1);
+            const uint32_t len = __builtin_amdgcn_readfirstlane(blen_s[bi]);
+            const uint32_t phys = __builtin_amdgcn_readfirstlane(bphys[bi]);
+            const K* kp = blockat(Ak, Tk, phys, two_sigma, log2b);
             K x[U];
+            if (o0 + U * 64 <= len) {  // a whole piece of 1024 elements: no checks
+#pragma unroll
+                for (int j = 0; j < U; j++) x[j] = kp[o0 + j * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < U; j++) add(x[j]);
+                continue;
+            }
 #pragma unroll
             for (int j = 0; j < U; j++) {
-                const uint64_t sl = c + (uint64_t)j * NT + tid;
-                x[j] = sl < s1 ? Ak[sl] : (K)0;
+                const uint32_t o = o0 + j * 64 + lane;
+                x[j] = (uint32_t)j * 64 < 1u << plog && o < len ? kp[o] : (K)0;
             }
 #pragma unroll
             for (int j = 0; j < U; j++)
-                if (c + (uint64_t)j * NT + tid < s1)
-                    atomicAdd(mine + ((uint32_t)(x[j] >> shift) & dmask), 1u);
-        }
-    } else {
-        // each wave reads whole blocks, U * 64 slots at a time
-        const uint32_t lane = tid & 63, nblk = (uint32_t)(span >> log2b);
-        for (uint32_t i = wave; i < nblk; i += NW) {
-            const uint32_t len = blen_s[i];
-            const K* kp = blockat(Ak, Tk, bphys[i], two_sigma, log2b);
-            for (uint32_t c = 0; c < len; c += 64 * U) {
-                K x[U];
-#pragma unroll
-                for (int j = 0; j < U; j++) {
-                    const uint32_t o = c + j * 64 + lane;
-                    x[j] = o < len ? kp[o] : (K)0;
-                }
-#pragma unroll
-                for (int j = 0; j < U; j++)
-                    if (c + j * 64 + lane < len)
-                        atomicAdd(mine + ((uint32_t)(x[j] >> shift) & dmask), 1u);
-            }
+                if ((uint32_t)j * 64 < 1u << plog && o0 + j * 64 + lane < len) add(x[j]);
         }
     }
+    if (rm.vary && !rm.r && diff)
+        atomicOr((unsigned long long*)&vary_s, (unsigned long long)diff);
     __syncthreads();
     for (uint32_t d = tid; d < sigma; d += NT) {
-        uint32_t s = 0;
-        for (uint32_t c = 0; c < copies; c++) s += h[c * sigma + d];
-        cnt[(uint64_t)blockIdx.x * sigma + d] = s;
-        if (s && !plan) atomicAdd(csum + (uint64_t)(blockIdx.x / kScanRows) * sigma + d, s);
+        uint32_t s = 0;  // the copies from a start of this thread's own (banks)
+        for (uint32_t c = 0; c < copies; c++) s += h[(d << clog) + ((c + d) & (copies - 1))];
+        st_agent(cnt + (uint64_t)blockIdx.x * sigma + d, s);
     }
-    if (!plan) return;
-    __shared__ uint32_t last;
-    // release this thread's rows at agent scope (each thread its own stores: a
-    // barrier waits for none of them), then one thread counts the workgroup in
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (rm.vary && !rm.r && tid == 0 && vary_s)
+        __hip_atomic_fetch_or(rm.vary, vary_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The rows pass between workgroups by agent-scope stores and loads: each thread waits
+    // until its stores are done (a barrier waits for none of them), then one thread counts
+    // the workgroup in.  (An agent-scope release fence here writes back the whole L2 in
+    // every wave: 2.1 ms per pass at 2^28.)
+    const uint32_t ch = blockIdx.x / kScanRows, r0 = ch * kScanRows;
+    const uint32_t rows = min<uint32_t>(kScanRows, gridDim.x - r0);
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) last = atomicAdd(done, 1u) == gridDim.x - 1;
+    if (tid == 0) last = add_agent(csum + (uint64_t)ch * sigma, 1u) == rows - 1;
     __syncthreads();
     if (!last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the other workgroups' rows
-    const uint32_t rows = gridDim.x;
-    for (uint32_t d = tid; d < sigma; d += NT) {
-        uint32_t run = 0;
-        for (uint32_t u = 0; u < rows; u++) {
-            const uint32_t x = cnt[(uint64_t)u * sigma + d];
-            cnt[(uint64_t)u * sigma + d] = run;
-            run += x;
+    uint32_t* const part = h;  // the counts were read
+    static_assert(kHistWords >= NT && kHistWords >= 2048, "part holds max(NT, sigma) words");
+    scan_columns<NT>(cnt + (uint64_t)r0 * sigma, rows, sigma, part, csum + (uint64_t)ch * sigma);
+    const uint32_t chunks = (gridDim.x + kScanRows - 1) / kScanRows;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) {
+        last = add_agent(done, 1u) == chunks - 1;
+        if (last && rm.vary) {
+            if (!rm.r)
+                mode = round_mode(__hip_atomic_load(rm.vary, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT),
+                                  0, rm.nt, bits);
+            rm.mode[rm.r] = mode;
         }
+        mode_s = mode;
     }
+    __syncthreads();
+    if (!last) return;
+    scan_columns<NT>(csum, chunks, sigma, part, cnt + (uint64_t)(gridDim.x - 1) * sigma);
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();  // the totals row is written by this workgroup; h is free
-    plan_round<NT>(cnt + (uint64_t)(rows - 1) * sigma, sigma, log2b, h, h + sigma, h + 2 * sigma,
-                   pp.S, pp.Pidx, pp.Plen, pp.f, plan >= 2 ? pp.est : nullptr, plan == 3);
-}
-
-// In place, for every digit d: cnt[u * sigma + d] becomes sum_{u' < u} cnt[u' * sigma + d].
-// Workgroup c takes the rows of chunk c: it adds up the sums of the earlier
-// chunks, then runs through its own rows.
-//
-// The last row is past the input (its counts are zero), so it ends with the digit
-// totals of the round's input.  With plan != 0 the last workgroup, which wrote
-// that row, then makes the round's plan from it (plan_round: the closed forms of
-// Alg. 5 and 6, and with plan == 2 the element starts of Alg. 1).  Dynamic LDS:
-// 2 sigma + 8 words when planning.
-template <int NT>
-__global__ __launch_bounds__(NT) void k_column_scan(uint32_t* cnt, const uint32_t* csum,
-                                                    uint32_t rows, uint32_t sigma,
-                                                    uint32_t log2b, uint32_t plan, PlanPtrs p)
-{
-    const uint32_t c = blockIdx.x, r0 = c * kScanRows, r1 = min(rows, r0 + kScanRows);
-    for (uint32_t d = threadIdx.x; d < sigma; d += NT) {
-        // the earlier chunks' sums, eight loads in flight
-        uint32_t part[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        uint32_t i = 0;
-        for (; i + 8 <= c; i += 8) {
-#pragma unroll
-            for (uint32_t u = 0; u < 8; u++) part[u] += csum[(uint64_t)(i + u) * sigma + d];
-        }
-        for (; i < c; i++) part[0] += csum[(uint64_t)i * sigma + d];
-        uint32_t run = 0;
-#pragma unroll
-        for (uint32_t u = 0; u < 8; u++) run += part[u];
-        uint32_t x[kScanRows];
-#pragma unroll
-        for (int i = 0; i < kScanRows; i++)
-            x[i] = r0 + i < r1 ? cnt[(uint64_t)(r0 + i) * sigma + d] : 0u;
-#pragma unroll
-        for (int i = 0; i < kScanRows; i++) {
-            if (r0 + i < r1) cnt[(uint64_t)(r0 + i) * sigma + d] = run;
-            run += x[i];
-        }
-    }
-    if (plan && c + 1 == gridDim.x) {
-        extern __shared__ uint32_t sm[];
-        __syncthreads();  // the totals row was written by this workgroup
-        plan_round<NT>(cnt + (uint64_t)(rows - 1) * sigma, sigma, log2b, sm, sm + sigma,
-                       sm + 2 * sigma, p.S, p.Pidx, p.Plen, p.f, plan >= 2 ? p.est : nullptr,
-                       plan == 3);
-    }
+    const bool packed = mode_s == kModePacked;
+    plan_round<NT>(cnt + (uint64_t)(gridDim.x - 1) * sigma, sigma, log2b, h, h + sigma,
+                   h + 2 * sigma, pp.S, pp.Pidx, pp.Plen, pp.f,
+                   packed || plan == 2 ? pp.est : nullptr, packed);
 }
 
 }  // namespace rs

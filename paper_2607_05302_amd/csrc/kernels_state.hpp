@@ -138,17 +138,38 @@ __device__ void plan_round(const uint32_t* __restrict__ cnt, uint32_t sigma, uin
     __syncthreads();
 }
 
+// What the rounds of a one-call sort do, decided on the device (mode[r]): a round whose
+// digit is the same for every element would leave the logical sequence as it is and is
+// left out; the last of the others is packed (plan_round); the rounds after it are left
+// out too.  When no digit varies the last round runs, packed, so that finalize finds a
+// packed state.  vary: the bits in which any two keys differ, ORed together by round 0's
+// counting pass, which reads every key anyway.
+constexpr uint32_t kModeRun = 0, kModeSkip = 1, kModePacked = 2;
+struct RoundModes {
+    uint64_t* vary;   // null: every round runs, packed as the host says
+    uint32_t* mode;   // [n_t]
+    uint32_t r, nt;
+};
+__device__ __forceinline__ uint32_t round_mode(uint64_t vary, uint32_t r, uint32_t nt,
+                                               uint32_t bits)
+{
+    const uint32_t last = vary ? (63u - (uint32_t)__builtin_clzll(vary)) / bits : nt - 1;
+    if (r == last) return kModePacked;
+    return (vary >> (bits * r)) & ((1ull << bits) - 1) ? kModeRun : kModeSkip;
+}
+
 // setup (Alg. 4): pi = [0..sigma) | 2 sigma .. sigma + f - 2 | sigma .. 2 sigma),
 // the n mod b tail of A copied to physical block sigma, the other pi buffer
 // cleared to "unset", f = sigma + floor(n/b) + 1 and P = the tail block, then
 // dummies (Pidx, Plen, f_out: index 0 of the per-round arrays); the first
-// round's look-back ring (ring_words words) cleared.
+// round's look-back ring (ring_words words) cleared.  Both pi buffers hold npx entries,
+// those from npi on (a packed round's extra blocks) unset.
 template <int KB, int VB>
 __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
                         typename Payload<VB>::T* __restrict__ Av,
                         typename UInt<KB>::T* __restrict__ Tk,
                         typename Payload<VB>::T* __restrict__ Tv, uint64_t n, uint32_t log2b,
-                        uint32_t sigma, uint32_t npi, uint32_t* __restrict__ pi,
+                        uint32_t sigma, uint32_t npi, uint32_t npx, uint32_t* __restrict__ pi,
                         uint32_t* __restrict__ pi_next, uint32_t* __restrict__ blen,
                         uint64_t* __restrict__ opened, uint32_t* __restrict__ Pidx,
                         uint32_t* __restrict__ Plen, uint32_t* __restrict__ f_out,
@@ -159,7 +180,7 @@ __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
         ring[i] = 0;
     const uint64_t nb = n >> log2b, tail = n - (nb << log2b);
     const uint32_t f = sigma + (uint32_t)nb + 1;
-    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < npi || i < tail;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < npx || i < tail;
          i += (uint64_t)gridDim.x * blockDim.x) {
         if (i < sigma) {
             Pidx[i] = i == 0 ? f - 1 : npi;  // the input tail, then dummies
@@ -176,6 +197,8 @@ __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
             // used lengths: full blocks, and the tail as logical f - 1 (Alg. 4)
             blen[L] = L + 1 == f ? (uint32_t)tail : (1u << log2b);
             if (L < sigma) opened[L] = 0;
+        } else if (i < npx) {
+            pi[i] = pi_next[i] = kEmpty;
         }
         if (i < tail) {
             uint64_t dst = ((uint64_t)sigma << log2b) + i;
@@ -195,12 +218,15 @@ __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
 // It also writes the used length of every logical block for the next round:
 // b, or the length recorded in P for the buckets' last blocks, and clears the
 // next round's look-back ring (ring_words words).
-__global__ void k_fixup(uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi_new,
-                        const uint32_t* __restrict__ S, const uint32_t* __restrict__ f_out,
-                        const uint32_t* __restrict__ Pidx, const uint32_t* __restrict__ Plen,
-                        uint32_t* __restrict__ blen, uint64_t* __restrict__ opened,
-                        uint32_t sigma, uint32_t log2b, uint32_t npi, uint32_t* __restrict__ ring,
-                        uint64_t ring_words)
+__device__ __forceinline__ void fixup(uint32_t* __restrict__ pi_old,
+                                      uint32_t* __restrict__ pi_new,
+                                      const uint32_t* __restrict__ S,
+                                      const uint32_t* __restrict__ f_out,
+                                      const uint32_t* __restrict__ Pidx,
+                                      const uint32_t* __restrict__ Plen,
+                                      uint32_t* __restrict__ blen, uint64_t* __restrict__ opened,
+                                      uint32_t sigma, uint32_t log2b, uint32_t npi,
+                                      uint32_t* __restrict__ ring, uint64_t ring_words)
 {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < ring_words;
          i += (uint64_t)gridDim.x * blockDim.x)
@@ -231,9 +257,11 @@ __global__ void k_fixup(uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi
 // 0 .. sigma - 1 of the round's input); the round drew the first f - 2 sigma
 // entries of its pool (the sigma extra blocks npi .., then pi[sigma ..]); the
 // entries it left fill logical blocks 0 .. sigma - 1 and f .. npi + sigma - 1.
-__global__ void k_pack_fixup(const uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi_new,
-                             const uint32_t* __restrict__ S, const uint32_t* __restrict__ f_out,
-                             uint32_t sigma, uint32_t npi)
+__device__ __forceinline__ void pack_fixup(const uint32_t* __restrict__ pi_old,
+                                           uint32_t* __restrict__ pi_new,
+                                           const uint32_t* __restrict__ S,
+                                           const uint32_t* __restrict__ f_out, uint32_t sigma,
+                                           uint32_t npi)
 {
     const uint32_t npx = npi + sigma, f = min(max(*f_out, 2 * sigma), npx);
     const uint32_t drawn = f - 2 * sigma;
@@ -246,6 +274,49 @@ __global__ void k_pack_fixup(const uint32_t* __restrict__ pi_old, uint32_t* __re
         } else if (j >= f) {
             pi_new[j] = pi_old[j - sigma];
         }
+    }
+}
+
+// pack_fixup after a packed round chosen by the host.  Index 0 of p is the round's own.
+__global__ void k_pack_fixup(const uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi_new,
+                             PlanPtrs p, uint32_t sigma, uint32_t npi)
+{
+    pack_fixup(pi_old, pi_new, p.S, p.f + 1, sigma, npi);
+}
+
+// The fixup of a round: by its mode in a one-call sort (mode not null), else the plain
+// one.  A round that was left out hands pi, P, f (and S and est, which finalize reads of
+// the last index) on as they are.  Index 0 of S, est, Pidx, Plen and f is the round's own.
+__global__ void k_fixup(uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi_new,
+                        PlanPtrs p, uint32_t* __restrict__ blen, uint64_t* __restrict__ opened,
+                        uint32_t sigma, uint32_t log2b, uint32_t npi, uint32_t npx,
+                        uint32_t* __restrict__ ring, uint64_t ring_words,
+                        const uint32_t* __restrict__ mode, uint32_t r)
+{
+    const uint32_t m = mode ? *mode : kModeRun;
+    if (m == kModeRun) {
+        fixup(pi_old, pi_new, p.S, p.f + 1, p.Pidx + sigma, p.Plen + sigma, blen, opened, sigma,
+              log2b, npi, ring, ring_words);
+    } else if (m == kModePacked) {
+        pack_fixup(pi_old, pi_new, p.S, p.f + 1, sigma, npi);
+    } else {
+        const uint32_t j0 = blockIdx.x * blockDim.x + threadIdx.x;
+        for (uint32_t j = j0; j < npx; j += gridDim.x * blockDim.x) {
+            pi_new[j] = pi_old[j];
+            pi_old[j] = kEmpty;
+        }
+        for (uint32_t d = j0; d < sigma; d += gridDim.x * blockDim.x) {
+            p.Pidx[sigma + d] = p.Pidx[d];
+            p.Plen[sigma + d] = p.Plen[d];
+            if (r) {
+                p.S[d] = p.S[(int64_t)d - sigma];
+                p.est[d] = p.est[(int64_t)d - sigma];
+            }
+        }
+        if (j0 == 0) p.f[1] = p.f[0];
+        // round 0 was counted before it was left out
+        for (uint64_t i = j0; !r && i < ring_words; i += (uint64_t)gridDim.x * blockDim.x)
+            ring[i] = 0;
     }
 }
 

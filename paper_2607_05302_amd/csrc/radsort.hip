@@ -142,6 +142,7 @@ struct Geo {
     uint32_t npi = 0, E = 0, tiles = 0, ring_w = 0, ring_log2 = 0;
     uint32_t st_log2 = 0;                 // tiles per super-tile: 2^st_log2
     uint32_t supers = 0, oop_supers = 0;  // super-tiles of a Radsort / out-of-place round
+    uint32_t lay_supers = 0;              // the super-tiles the workspace is laid out for
     uint32_t oop_E = 0, oop_st_log2 = 0;  // tile and super-tile of the out-of-place round
     bool fin_temps = false;       // finalize scratch holds the two-kernel F1's temporary blocks
     bool fin_temps_pack = false;  // the same for a packed state (n_pi + sigma blocks)
@@ -157,7 +158,8 @@ struct Layout {
         csum, stcnt, fin, alt_k, alt_v;
     uint64_t Xk, Xv, pack;  // a packed last round only: sigma extra blocks, bucket table
     uint64_t consumed;  // ordering-check builds only: a tag per physical block
-    uint64_t ring_bytes, fin_bytes, total;
+    uint64_t zero, zero_bytes;  // what each round finds zeroed: ring, counters, chunk sums
+    uint64_t fin_bytes, total;
 };
 
 template <bool WIDE, bool OOP> uint32_t tile_elems_t(uint32_t kb, uint32_t vb)
@@ -188,6 +190,18 @@ uint32_t device_cus()
         return 256;
     }
     return (uint32_t)cus;
+}
+
+// Bytes of the round's counting state: the look-back count words, the digit starts of
+// `supers` super-tiles (and a row of totals), and their chunk sums.
+uint64_t count_word_bytes(const Geo& g) { return 4ull * g.sigma * g.ring_w; }
+uint64_t digit_start_bytes(const Geo& g, uint64_t supers)
+{
+    return align_up(4ull * g.sigma * (supers + 1), 256);
+}
+uint64_t csum_bytes(const Geo& g, uint64_t supers)
+{
+    return align_up(4ull * g.sigma * ((supers + kScanRows) / kScanRows), 256);
 }
 
 int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bits,
@@ -253,7 +267,17 @@ int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bit
         return std::max<uint32_t>(kSuperSlotsLog2 > elog ? kSuperSlotsLog2 - elog : 0u,
                                   g.log2b > elog ? g.log2b - elog : 0u);
     };
-    g.st_log2 = super_log2(g.E);
+    const uint32_t lay_st = super_log2(lay_E);
+    g.lay_supers = (lay_tiles + (1u << lay_st) - 1) >> lay_st;
+    // One tile per super-tile (no look-back, and a counting pass of many small
+    // workgroups) where its rows fit the memory laid out for the ring and the larger
+    // super-tiles' rows; else super-tiles of at least 2^kSuperSlotsLog2 slots.  At
+    // 2^20 uint32 pairs super-tiles of 2^16 slots were 17 workgroups: 20 us per pass.
+    g.st_log2 = digit_start_bytes(g, g.tiles) + csum_bytes(g, g.tiles) <=
+                        count_word_bytes(g) + csum_bytes(g, g.lay_supers) +
+                            digit_start_bytes(g, g.lay_supers)
+                    ? 0u
+                    : super_log2(g.E);
     g.supers = (g.tiles + (1u << g.st_log2) - 1) >> g.st_log2;
     g.oop_st_log2 = super_log2(g.oop_E);
     const uint64_t oop_tiles = (n + g.oop_E - 1) / g.oop_E;
@@ -322,23 +346,30 @@ Layout make_layout(const Geo& g, bool oop, bool pack = false)
 #ifdef RS_DEBUG_ORDER
     L.consumed = oop ? 0 : take(4ull * g.npi);
 #endif
-    // the look-back ring (count words, done words) and the chunk sums of the
-    // super-tile scan, zeroed before each round; then the super-tile digit starts.
-    // Finalize reuses all of it.
+    // the look-back ring (count words, done words), the tile counter of the round kernel
+    // and the counter of the counting kernel, the chunk sums of the super-tile scan, zeroed
+    // before each round; then the super-tile digit starts, with one more row for the
+    // digit totals.  Finalize reuses all of it.
     const uint64_t supers = oop ? g.oop_supers : g.supers;
-    const uint64_t agg_bytes = 4ull * g.ring_w * sig;
-    // + the tile counter of the round kernel and the counter of the counting kernel
+    const uint64_t lay_supers = oop ? g.oop_supers : g.lay_supers;
     const uint64_t done_bytes = align_up(4ull * g.ring_w + 8, 256);
-    // one more row than super-tiles: the column scan leaves the digit totals there
-    const uint64_t csum_bytes = align_up(4ull * ((supers + kScanRows) / kScanRows) * sig, 256);
-    L.ring_bytes = agg_bytes + done_bytes + csum_bytes;
-    const uint64_t st_bytes = align_up(4ull * (supers + 1) * sig, 256);
     L.fin_bytes = oop ? 0 : finalize_bytes(g, pack);
-    L.ring = take(std::max(L.ring_bytes + st_bytes, L.fin_bytes));
-    L.agg = L.ring;
-    L.done = L.ring + agg_bytes;
-    L.csum = L.done + done_bytes;
-    L.stcnt = L.ring + L.ring_bytes;
+    L.ring = take(std::max(count_word_bytes(g) + done_bytes + csum_bytes(g, lay_supers) +
+                               digit_start_bytes(g, lay_supers),
+                           L.fin_bytes));
+    if (!oop && g.st_log2 == 0) {
+        // no count words: the digit starts take their place (make_geo checks the room)
+        L.stcnt = L.agg = L.ring;
+        L.zero = L.csum = L.stcnt + digit_start_bytes(g, supers);
+        L.done = L.csum + csum_bytes(g, supers);
+        L.zero_bytes = csum_bytes(g, supers) + done_bytes;
+    } else {
+        L.zero = L.agg = L.ring;
+        L.done = L.ring + count_word_bytes(g);
+        L.csum = L.done + done_bytes;
+        L.zero_bytes = count_word_bytes(g) + done_bytes + csum_bytes(g, supers);
+        L.stcnt = L.ring + L.zero_bytes;
+    }
     L.fin = L.ring;
     L.total = o;
     return L;
@@ -446,6 +477,12 @@ struct radsort_state {
         return PlanPtrs{u32(L.S), u32(L.Pidx), u32(L.Plen), u32(L.f), u32(L.est)};
     }
     uint32_t* err() const { return u32(L.ctr) + g.nt; }
+    // one-call sorts on the tile kernel decide each round's mode on the device: mode
+    // words 0 .. n_t - 1 of the counters, the 64-bit `vary` word past the error word
+    bool modes() const { return pack && g.tile && msd_shift < 0; }
+    uint64_t* vary() const { return (uint64_t*)(u32(L.ctr) + ((g.nt + 3) & ~1u)); }
+    // entries of pi: a packed round's extra blocks too
+    uint32_t npx() const { return g.npi + (pack ? g.sigma : 0u); }
 };
 
 namespace {
@@ -501,17 +538,16 @@ int launch_persistent(const void* kern, uint32_t tiles, uint32_t threads, Args& 
     return RADSORT_OK;
 }
 
-// Digit counts of every super-tile of a round's input, then their column scan:
-// stcnt[u][d] = elements with digit d before super-tile u, for u = 0 .. supers;
-// row `supers` (past the input, counted as empty) ends with the digit totals of
-// the round's input, from which the scan's last workgroup makes the plan of round
-// r (S[r], P[r+1], f[r+1], and est[r] for the out-of-place round).
+// Digit starts of every super-tile of a round's input and the plan of round r from the
+// digit totals (S[r], P[r+1], f[r+1], and est[r] for the out-of-place or packed round):
+// one launch (k_supertile_counts).  Row `supers` of stcnt, past the input, ends with the
+// digit totals.
 template <int KB, bool OOP>
 void launch_super_counts(const Geo& g, const typename UInt<KB>::T* Ak,
                          const typename UInt<KB>::T* Tk, const uint32_t* pi,
                          const uint32_t* blen, const uint32_t* f_in, uint32_t shift,
                          uint32_t* stcnt, uint32_t* csum, uint32_t* err, uint32_t* done_ctr,
-                         uint32_t r, PlanPtrs p, hipStream_t s, bool packed = false)
+                         uint32_t r, PlanPtrs p, hipStream_t s, bool packed, RoundModes rm)
 {
     const uint32_t rows = (OOP ? g.oop_supers : g.supers) + 1;
     const uint32_t sts_log2 = OOP ? g.oop_st_log2 + (uint32_t)ilog2(g.oop_E)
@@ -519,15 +555,16 @@ void launch_super_counts(const Geo& g, const typename UInt<KB>::T* Ak,
     const uint32_t sig = g.sigma, plan = OOP ? 2u : packed ? 3u : 1u;
     PlanPtrs pr{p.S + r * sig, p.Pidx + (r + 1) * sig, p.Plen + (r + 1) * sig, p.f + r + 1,
                 p.est + r * sig};
-    // one chunk of rows: the counting kernel's last workgroup scans and plans
-    const bool fused = rows <= kScanRows;
-    hipLaunchKernelGGL((k_supertile_counts<KB, OOP, 1024>), dim3(rows), dim3(1024), 0, s, Ak, Tk,
-                       pi, blen, f_in, g.n, shift, g.bits, g.log2b, g.npi, sts_log2, stcnt, csum,
-                       err, done_ctr, fused ? plan : 0u, pr);
-    if (!fused)
-        hipLaunchKernelGGL(k_column_scan<256>, dim3((rows + kScanRows - 1) / kScanRows),
-                           dim3(256), 4 * (2 * sig + 8), s, stcnt, csum, rows, sig, g.log2b, plan,
-                           pr);
+    // 512 threads, four workgroups to a compute unit, or 1024 where there is at most one
+    // super-tile per compute unit (2^24 pairs, 1042 rows: 30 against 38 us; 2^20 pairs,
+    // 162 rows: 17.5 against 15.5 us)
+    auto launch = [&](auto kern, uint32_t threads) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, Ak, Tk, pi, blen, f_in, g.n, shift,
+                           g.bits, g.log2b, g.npi, sts_log2, stcnt, csum, err, done_ctr, plan, pr,
+                           rm);
+    };
+    if (rows <= 256) launch(k_supertile_counts<KB, OOP, 1024>, 1024);
+    else launch(k_supertile_counts<KB, OOP, 512>, 512);
 }
 
 // The claimed forms (no co-residency needed): one workgroup per tile, or for the
@@ -633,14 +670,14 @@ template <int KB, int VB> struct Ops {
         g_timer.mark(kStart, 0, s);
         // every round is planned later from its own digit counts
         launch_fill(st->u32(st->L.ctr), g.nt + 8, 0, s);
-        uint64_t work = std::max<uint64_t>(g.npi, g.n & (g.b - 1));
+        uint64_t work = std::max<uint64_t>(st->npx(), g.n & (g.b - 1));
         uint32_t grid = (uint32_t)std::min<uint64_t>((work + 255) / 256, 4096);
         hipLaunchKernelGGL((k_setup<KB, VB>), dim3(grid), dim3(256), 0, s, (K*)st->keys,
                            (V*)st->vals, (K*)(st->ws + st->L.Tk), (V*)(st->ws + st->L.Tv), g.n,
-                           g.log2b, g.sigma, g.npi, st->pi(0), st->pi(1), st->u32(st->L.blen),
+                           g.log2b, g.sigma, g.npi, st->npx(), st->pi(0), st->pi(1), st->u32(st->L.blen),
                            (uint64_t*)(st->ws + st->L.opened), st->u32(st->L.Pidx),
-                           st->u32(st->L.Plen), st->u32(st->L.f), st->u32(st->L.ring),
-                           st->L.ring_bytes / 4);
+                           st->u32(st->L.Plen), st->u32(st->L.f), st->u32(st->L.zero),
+                           st->L.zero_bytes / 4);
         g_timer.mark(kSetupEnd, 0, s);
         st->cur = 0;
         st->rounds_done = 0;
@@ -720,15 +757,21 @@ template <int KB, int VB> struct Ops {
         a.npi = g.npi;
         a.ring_log2 = g.ring_log2;
         a.st_log2 = g.st_log2;
-        // the last round of a packed sort (plan_round, k_round): its buckets start at
-        // their final offsets and it draws from sigma extra blocks first
-        const bool packed = st->pack && r + 1 == g.nt && st->msd_shift < 0;
-        a.npi_x = packed ? g.npi + g.sigma : g.npi;
-        if (packed) {
+        // the last round of a packed sort (plan_round): its buckets start at their final
+        // offsets and it draws from sigma extra blocks first.  Which round that is, and
+        // which ones are left out, the device decides where the tile kernel runs (modes).
+        const bool modes = st->modes();
+        const bool packed = st->pack && !modes && r + 1 == g.nt && st->msd_shift < 0;
+        a.npi_x = packed || modes ? g.npi + g.sigma : g.npi;
+        if (packed || modes) {
             a.pack_est = st->u32(st->L.est) + r * g.sigma;
             a.Xk = (K*)(st->ws + st->L.Xk);
             a.Xv = (V*)(st->ws + st->L.Xv);
-            launch_fill(a.pi_new + g.npi, g.sigma, kEmpty, s);  // entries past n_pi unset
+        }
+        RoundModes rm{};
+        if (modes) {
+            a.mode = st->u32(st->L.ctr) + r;
+            rm = RoundModes{st->vary(), st->u32(st->L.ctr), r, g.nt};
         }
 #ifdef RS_TIMELINE
         a.tl = g.tiles <= g_tl_tiles ? g_tl : nullptr;
@@ -740,27 +783,28 @@ template <int KB, int VB> struct Ops {
 #endif
         uint32_t* stcnt = (uint32_t*)(st->ws + st->L.stcnt);
         a.stbase = stcnt;
+        a.stsum = st->u32(st->L.csum);
         // the ring is clear: setup or the previous round's fixup cleared it
         g_timer.mark(kCountBegin, r, s);
         launch_super_counts<KB, false>(g, a.Ak, a.Tk, a.pi_old, a.blen, a.f_in, a.shift, stcnt,
                                        st->u32(st->L.csum), a.err, a.tile_ctr + 1, r,
-                                       st->plan(), s, packed);
+                                       st->plan(), s, packed, rm);
         g_timer.mark(kRoundBegin, r, s);
         int rc = launch_round_t<KB, VB, false>(g, a, s, st->dynamic, st->seq_draws);
         if (rc) return rc;
         g_timer.mark(kRoundEnd, r, s);
         uint32_t grid = (uint32_t)std::min<uint64_t>((a.npi_x + 255) / 256, 4096);
+        PlanPtrs p = st->plan();
+        p = PlanPtrs{p.S + r * g.sigma, p.Pidx + r * g.sigma, p.Plen + r * g.sigma, p.f + r,
+                     p.est + r * g.sigma};
         if (packed)
             hipLaunchKernelGGL(k_pack_fixup, dim3(grid), dim3(256), 0, s, st->pi(st->cur),
-                               st->pi(st->cur ^ 1), a.S, st->u32(st->L.f) + r + 1, g.sigma,
-                               g.npi);
+                               st->pi(st->cur ^ 1), p, g.sigma, g.npi);
         else
             hipLaunchKernelGGL(k_fixup, dim3(grid), dim3(256), 0, s, st->pi(st->cur),
-                               st->pi(st->cur ^ 1), a.S, st->u32(st->L.f) + r + 1,
-                               st->u32(st->L.Pidx) + (r + 1) * g.sigma,
-                               st->u32(st->L.Plen) + (r + 1) * g.sigma, st->u32(st->L.blen),
-                               a.opened, g.sigma, g.log2b, g.npi, st->u32(st->L.ring),
-                               st->L.ring_bytes / 4);
+                               st->pi(st->cur ^ 1), p, st->u32(st->L.blen), a.opened, g.sigma,
+                               g.log2b, g.npi, a.npi_x, st->u32(st->L.zero), st->L.zero_bytes / 4,
+                               a.mode, r);
         g_timer.mark(kFixupEnd, r, s);
         st->cur ^= 1;
         st->rounds_done++;
@@ -879,11 +923,12 @@ template <int KB, int VB> struct Ops {
             a.st_log2 = g.oop_st_log2;
             uint32_t* stcnt = (uint32_t*)(ws + L.stcnt);
             a.stbase = stcnt;
-            launch_fill((uint32_t*)a.agg, L.ring_bytes / 4, 0, s);
+            a.stsum = (uint32_t*)(ws + L.csum);
+            launch_fill((uint32_t*)(ws + L.zero), L.zero_bytes / 4, 0, s);
             g_timer.mark(kCountBegin, r, s);
             launch_super_counts<KB, true>(g, a.Ak, (const K*)nullptr, nullptr, nullptr, nullptr,
                                           a.shift, stcnt, (uint32_t*)(ws + L.csum), a.err,
-                                          a.tile_ctr + 1, r, p, s);
+                                          a.tile_ctr + 1, r, p, s, false, RoundModes{});
             g_timer.mark(kRoundBegin, r, s);
             int rc = launch_round_t<KB, VB, true>(g, a, s, dyn);
             if (rc) return rc;

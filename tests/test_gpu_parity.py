@@ -428,3 +428,41 @@ def test_tile_edges_match_oracle(case):
         if vb:
             assert np.array_equal(from_dev(gv, vb).astype(np.uint64), ev)
     st.close()
+
+
+# ---------------------------------------------------------------- rounds left out
+
+# Keys whose digits vary at some positions only (vary: the mask of the bits that do): the
+# one-call sort leaves out the rounds of the others and packs the last one that runs,
+# wherever it is; no bit varies at all; one element differs from all the others.
+VARY = [
+    (0x000000FF, 50001, 4, 4, 8, 1024),
+    (0x0000FF00, (1 << 22) + 3, 4, 4, 8, 2048),
+    (0xFF0000FF, 300000, 4, 0, 8, 1024),
+    (0x00FF0000, 70001, 4, 8, 4, 1024),
+    (0x0, 40000, 4, 4, 8, 1024),
+    (0x80000000, 123457, 4, 4, 6, 1024),
+    (0xFF << 56, (1 << 20) + 9, 8, 4, 8, 1024),
+    (0xF << 28 | 1, 90000, 8, 0, 8, 4096),
+    (0x0, (1 << 20) + 1, 8, 8, 8, 1024),
+    (0xFFFF << 20, 200003, 8, 4, 5, 1024),
+]
+
+
+@pytest.mark.parametrize("shared", [False, True], ids=["alone", "shared"])
+@pytest.mark.parametrize("case", VARY, ids=lambda c: "-".join(map(str, c)))
+def test_constant_digits_match_oracle(case, shared):
+    mask, n, kb, vb, bits, b = case
+    say(f"constant digits {case} shared={shared}")
+    keys, vals = inputs("uniform", n, kb, vb, seed=9)
+    fixed = keys.dtype.type(0x5A5A5A5AA5A5A5A5 & ((1 << 8 * kb) - 1))
+    keys = (keys & keys.dtype.type(mask)) | (fixed & keys.dtype.type(~mask & ((1 << 8 * kb) - 1)))
+    if mask == 0 and kb == 8:
+        keys[n // 3] ^= np.uint64(1 << 40)
+    sigma, nt = oracle.digit_params(kb, bits)
+    dk, dv = to_dev(keys), to_dev(vals) if vb else None
+    radsort.sort_(dk, dv, digit_bits=bits, block_elems=b, check=True, shared=shared)
+    ek, ev = oracle.radsort(keys, vals, sigma, nt, b)
+    assert np.array_equal(from_dev(dk, kb).astype(np.uint64), ek)
+    if vb:
+        assert np.array_equal(from_dev(dv, vb).astype(np.uint64), ev)
