@@ -39,6 +39,97 @@ __device__ __forceinline__ uint32_t opaque(uint32_t x)
 // hold its inputs instead).
 __device__ __forceinline__ void pin(uint32_t& x) { asm volatile("" : "+v"(x)); }
 
+// Stable rank of every element of a wave among the wave's elements of the same digit, in
+// slot order (item j of all lanes before item j + 1), two 16-bit ranks per word of rp
+// (0xFFFF: no element; nvalid bit j: item j of this lane holds one; wfull: all of them
+// do).  myh: the wave's digit counts, zero on entry, complete on return; myor: its OR
+// table, zero on entry (OR only).  items: the items looked at; the rest are empty and their
+// words of rp left as they are.
+template <int FB, bool OR, typename K, int ITEMS>
+__device__ __forceinline__ void rank_wave(const K (&key)[ITEMS], uint32_t nvalid, bool wfull,
+                                          uint32_t shift, uint32_t bits, uint16_t* myh,
+                                          uint64_t* myor, uint32_t (&rp)[ITEMS / 2],
+                                          int items = ITEMS)
+{
+    const uint32_t lane = lane_id(), dmask = (1u << bits) - 1;
+    // Lanes with the same digit as this one, found bit by bit on the vector unit, or
+    // through the wave's OR table: each lane ORs its bit into the word of its digit
+    // and reads the word back.  Lower lanes of the set come first (slot order); the
+    // highest one commits the set's count.
+    auto match = [&](uint32_t dw, uint64_t vm) {
+        uint32_t lo = (uint32_t)vm, hi = (uint32_t)(vm >> 32);
+#pragma unroll
+        for (uint32_t k = 0; k < (FB ? FB : 8); k++) {
+            if (FB || k < bits) {
+                // nb: all ones where the lane's bit k is set; its peers are the lanes
+                // whose bit is the same: p & ~(ballot ^ nb)
+                const uint32_t nb = (uint32_t)__builtin_amdgcn_sbfe((int)dw, k, 1);
+                const uint64_t bk = ballot(nb != 0);
+                lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bk, nb, 0x90);
+                hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bk >> 32), nb, 0x90);
+            }
+        }
+        return (uint64_t)hi << 32 | lo;
+    };
+    auto commit = [&](uint32_t dg, uint64_t peers, bool clear) {
+        const uint32_t old = myh[dg];
+        if ((peers >> lane) == 1ull) {  // highest lane of the set
+            myh[dg] = (uint16_t)(old + (uint32_t)__popcll(peers));
+            if (clear) myor[dg] = 0;
+        }
+        return old + popc_below(peers);
+    };
+    auto put_rank = [&](int j, uint32_t r) {
+        if (j & 1) rp[j / 2] |= r << 16;
+        else rp[j / 2] = r;
+        pin(rp[j / 2]);
+    };
+    auto by_ballot = [&](auto full, int from) {
+#pragma unroll
+        for (int j = 0; j < ITEMS; j++) {
+            if (j < from) continue;
+            if (j >= items) break;
+            if constexpr (ITEMS >= 32) __builtin_amdgcn_sched_barrier(0);  // registers
+            const uint32_t dw = (uint32_t)(key[j] >> shift);
+            uint32_t r = 0xFFFFu;
+            if constexpr (full.value) {
+                r = commit(dw & dmask, match(dw, ~0ull), false);
+            } else {
+                const bool valid = nvalid >> j & 1u;
+                const uint64_t peers = match(dw, ballot(valid));
+                if (valid) r = commit(dw & dmask, peers, false);
+            }
+            put_rank(j, r);
+        }
+    };
+    if (!wfull) {
+        by_ballot(std::false_type{}, 0);
+    } else if constexpr (!OR) {
+        by_ballot(std::true_type{}, 0);
+    } else {
+        // the first item tells a wave of skewed digits (six or more equal ones), whose
+        // table accesses would serialise
+        const uint32_t dw0 = (uint32_t)(key[0] >> shift);
+        const uint64_t peers0 = match(dw0, ~0ull);
+        put_rank(0, commit(dw0 & dmask, peers0, false));
+        if (ballot(__popcll(peers0) >= 6) != 0) {
+            by_ballot(std::true_type{}, 1);
+        } else {
+            const uint64_t mybit = 1ull << lane;
+#pragma unroll
+            for (int j = 1; j < ITEMS; j++) {
+                if (j >= items) break;
+                if constexpr (ITEMS >= 32) __builtin_amdgcn_sched_barrier(0);  // registers
+                const uint32_t dg = (uint32_t)(key[j] >> shift) & dmask;
+                __hip_atomic_fetch_or(myor + dg, mybit, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+                const uint64_t peers = myor[dg];
+                put_rank(j, commit(dg, peers, true));
+            }
+        }
+    }
+}
+
 template <int KB, int VB, int FB, class SH>
 __global__ __launch_bounds__(SH::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB> a)
@@ -181,82 +272,7 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     if constexpr (OR_RANK)
         for (uint32_t i = lane; i < SMAX; i += 64) myor[i] = 0;
     uint32_t rp[ITEMS / 2];  // ranks, later staged positions; 0xFFFF: no element
-    {
-        // Lanes with the same digit as this one, found bit by bit on the vector unit, or
-        // through the wave's OR table: each lane ORs its bit into the word of its digit
-        // and reads the word back.  Lower lanes of the set come first (slot order); the
-        // highest one commits the set's count.
-        auto match = [&](uint32_t dw, uint64_t vm) {
-            uint32_t lo = (uint32_t)vm, hi = (uint32_t)(vm >> 32);
-#pragma unroll
-            for (uint32_t k = 0; k < (FB ? FB : 8); k++) {
-                if (FB || k < bits) {
-                    // nb: all ones where the lane's bit k is set; its peers are the lanes
-                    // whose bit is the same: p & ~(ballot ^ nb)
-                    const uint32_t nb = (uint32_t)__builtin_amdgcn_sbfe((int)dw, k, 1);
-                    const uint64_t bk = ballot(nb != 0);
-                    lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bk, nb, 0x90);
-                    hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bk >> 32), nb, 0x90);
-                }
-            }
-            return (uint64_t)hi << 32 | lo;
-        };
-        auto commit = [&](uint32_t dg, uint64_t peers, bool clear) {
-            const uint32_t old = myh[dg];
-            if ((peers >> lane) == 1ull) {  // highest lane of the set
-                myh[dg] = (uint16_t)(old + (uint32_t)__popcll(peers));
-                if (clear) myor[dg] = 0;
-            }
-            return old + popc_below(peers);
-        };
-        auto put_rank = [&](int j, uint32_t r) {
-            if (j & 1) rp[j / 2] |= r << 16;
-            else rp[j / 2] = r;
-            pin(rp[j / 2]);
-        };
-        auto by_ballot = [&](auto full, int from) {
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++) {
-                if (j < from) continue;
-                __builtin_amdgcn_sched_barrier(0);
-                const uint32_t dw = (uint32_t)(key[j] >> a.shift);
-                uint32_t r = 0xFFFFu;
-                if constexpr (full.value) {
-                    r = commit(dw & dmask, match(dw, ~0ull), false);
-                } else {
-                    const bool valid = nvalid >> j & 1u;
-                    const uint64_t peers = match(dw, ballot(valid));
-                    if (valid) r = commit(dw & dmask, peers, false);
-                }
-                put_rank(j, r);
-            }
-        };
-        if (!wfull) {
-            by_ballot(std::false_type{}, 0);
-        } else if constexpr (!OR_RANK) {
-            by_ballot(std::true_type{}, 0);
-        } else {
-            // the first item tells a wave of skewed digits (six or more equal ones), whose
-            // table accesses would serialise
-            const uint32_t dw0 = (uint32_t)(key[0] >> a.shift);
-            const uint64_t peers0 = match(dw0, ~0ull);
-            put_rank(0, commit(dw0 & dmask, peers0, false));
-            if (ballot(__popcll(peers0) >= 6) != 0) {
-                by_ballot(std::true_type{}, 1);
-            } else {
-                const uint64_t mybit = 1ull << lane;
-#pragma unroll
-                for (int j = 1; j < ITEMS; j++) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    const uint32_t dg = (uint32_t)(key[j] >> a.shift) & dmask;
-                    __hip_atomic_fetch_or(myor + dg, mybit, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_WORKGROUP);
-                    const uint64_t peers = myor[dg];
-                    put_rank(j, commit(dg, peers, true));
-                }
-            }
-        }
-    }
+    rank_wave<FB, OR_RANK>(key, nvalid, wfull, a.shift, bits, myh, myor, rp);
     for (uint32_t j = rq + tid; j < rqend; j += NT) {
         const uint32_t* w = a.done + (j & wmask);
         uint32_t v = j == rq + tid ? rv : ld_agent(w), spins = 0;

@@ -1,135 +1,166 @@
-// Sorting many small arrays at once: one workgroup sorts one array entirely in
-// LDS and registers, so it needs no extra device memory at all.  This is the
-// regime the paper hands to an out-of-place sort (arrays smaller than T, Sec. 5):
-// on the GPU an array of up to E records fits on chip.
+// Sorting small arrays whole on chip: one workgroup sorts one array in LDS and
+// registers, so it needs no extra device memory at all.  This is the regime the paper
+// hands to an out-of-place sort (arrays smaller than T, Sec. 5).
 //
-// Workgroup i takes array i, elements [offsets[i], offsets[i+1]) of the key and
-// payload planes, if it has at most E elements (larger arrays are left alone).
-// Each of the n_t rounds is the stable counting sort of Alg. 1 on the digit of
-// that round: the records are in registers in their current order (slot s =
-// wave * SEG + j * 64 + lane), ranked per wave with the same OR-table scheme as
-// the round kernel, and written to LDS at digit start + rank; they are read
-// back in slot order for the next round.
+// Workgroup i takes array i (elements [offsets[i], offsets[i+1]) of the key and payload
+// planes), or with a claim counter (zero on entry) one array after another, and sorts it if
+// it has lo < n <= E elements; with offsets null the one array of n1 elements.  The array is dealt out over all the waves, ceil(n / NT) items
+// to a lane (slot s = wave * 64 items + j * 64 + lane).  Each round is the stable counting
+// sort of Alg. 1 on 8 bits: ranks within the waves by ballots (rank_wave), digit and wave
+// starts by scans, the records to LDS at start + rank and back in slot order.  A round
+// whose digit is the same for every element is left out.
+//
+// What bounds it: the latency of a round's steps (ranks of `items` items, the barriers, two
+// scans), so a short array takes few items per lane and a small workgroup, and the payload
+// is staged in the keys' bytes after them, which lets four workgroups of the large shape
+// share a compute unit.  16384 arrays of 1911 .. 2048 uint32 pairs: 752 us with one shape of
+// 8192 slots, 319 us with the short one; 4096 arrays of 7643 .. 8192 pairs 372 and 363 us;
+// one array of 1500 pairs 290 us through the general path, 36 us here (the copy of the
+// input and the wait for the stream included).
 #pragma once
 
 #include "common.hpp"
+#include "kernel_tile.hpp"
 
 namespace rs {
 
 template <int KB, int VB, int WAVES, int ITEMS>
-__global__ __launch_bounds__(WAVES * 64) void k_sort_small(typename UInt<KB>::T* keys,
-                                                           typename Payload<VB>::T* vals,
-                                                           const uint64_t* offsets,
-                                                           uint32_t nseg, uint32_t bits,
-                                                           uint32_t nt, uint32_t* err)
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_sort_small(
+    typename UInt<KB>::T* keys, typename Payload<VB>::T* vals, const uint64_t* offsets,
+    uint32_t nseg, uint64_t n1, uint32_t lo, uint32_t* err, uint32_t* claim)
 {
     using K = typename UInt<KB>::T;
     using V = typename Payload<VB>::T;
-    constexpr int NT = WAVES * 64;
-    constexpr int E = NT * ITEMS;
-    constexpr int SEG = E / WAVES;
-    constexpr int SMAX = 256;
-    static_assert(E * KB >= WAVES * SMAX * 8, "OR tables live in the key stage");
-    __shared__ K lk[E];
-    __shared__ V lv[VB ? E : 1];
-    __shared__ uint32_t wh[WAVES * SMAX];
-    __shared__ uint32_t excl[SMAX];
-    __shared__ uint32_t tmp[NT / 64 + 1];
+    constexpr int NT = WAVES * 64, E = NT * ITEMS, SMAX = 256, DW = SMAX / 64;
+    static_assert(NT >= SMAX, "one digit per thread");
+    static_assert(E <= 32768, "16-bit positions");
+    // the keys in sorted order, then the payload in the same bytes
+    __shared__ __align__(16) unsigned char stage[E * (KB > VB ? KB : VB)];
+    K* const lk = (K*)stage;
+    V* const lv = (V*)stage;
+    __shared__ __align__(16) uint16_t wh[WAVES * SMAX];
+    __shared__ uint32_t tmp[DW];
+    __shared__ uint64_t vary;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t sigma = 1u << bits, dmask = sigma - 1;
-    if (blockIdx.x >= nseg) return;
-    const uint64_t o0 = offsets[blockIdx.x], o1 = offsets[blockIdx.x + 1];
-    if (o1 <= o0 + 1 || o1 - o0 > (uint64_t)E) return;  // nothing to do, or a large array
-    if (bits > 8) {  // never for a call made by the library
-        if (tid == 0) raise_error(err, kErrBounds);
-        return;
+    if (!offsets && blockIdx.x == 0 && tid == 0 && err) *err = 0;  // the call's error word
+
+    // the workgroup's own array, or with a claim counter one array after another
+    __shared__ uint32_t claimed;
+    for (uint32_t i = blockIdx.x;; i = claimed) {
+    if (claim) {
+        __syncthreads();  // the array before is done with LDS
+        if (tid == 0) claimed = add_agent(claim, 1u);
+        __syncthreads();
+        i = claimed;
     }
-    const uint32_t n = (uint32_t)(o1 - o0);
-    K* kp = keys + o0;
+    if (i >= nseg) return;
+    uint64_t o0 = 0, n64 = n1;
+    if (offsets) {
+        o0 = offsets[i];
+        const uint64_t o1 = offsets[i + 1];
+        n64 = o1 > o0 ? o1 - o0 : 0;
+    }
+    if (n64 <= max(lo, 1u) || n64 > (uint64_t)E) {  // nothing to do, or another's
+        if (!claim) return;
+        continue;
+    }
+    const uint32_t n = (uint32_t)n64;
+    const int items = (int)((n + NT - 1) / NT);
+    const uint32_t s0 = wave * 64 * items + lane;
+    K* const kp = keys + o0;
     V* vp = nullptr;
     if constexpr (VB != 0) vp = vals + o0;
+    if (tid == 0) vary = 0;
 
     K key[ITEMS];
     V val[ITEMS];
+    uint32_t nvalid = 0;
+    const K ref = kp[0];
+    K diff = 0;
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
-        const uint32_t s = wave * SEG + j * 64 + lane;
-        key[j] = s < n ? kp[s] : (K)0;
-        if constexpr (VB != 0) val[j] = s < n ? vp[s] : (V)0;
+        key[j] = 0;
+        if (j < items && s0 + j * 64 < n) {
+            key[j] = kp[s0 + j * 64];
+            if constexpr (VB != 0) val[j] = vp[s0 + j * 64];
+            nvalid |= 1u << j;
+        }
     }
-    for (uint32_t r = 0; r < nt; r++) {
-        const uint32_t shift = bits * r;  // round r sorts by key position n_t - 1 - r
-        uint64_t* myor = (uint64_t*)lk + wave * SMAX;
-        uint32_t* myh = wh + wave * SMAX;
-        for (uint32_t i = lane; i < SMAX; i += 64) {
-            myor[i] = 0;
-            myh[i] = 0;
-        }
-        __syncthreads();
-        uint32_t rk[ITEMS];
-        const uint64_t mybit = 1ull << lane;
 #pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            const uint32_t s = wave * SEG + j * 64 + lane;
-            rk[j] = ~0u;
-            if (s < n) {
-                const uint32_t d = (uint32_t)(key[j] >> shift) & dmask;
-                __hip_atomic_fetch_or(myor + d, mybit, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_WORKGROUP);
-                const uint64_t peers = myor[d];
-                const uint32_t old = myh[d];
-                if ((peers >> lane) == 1ull) {
-                    myh[d] = old + (uint32_t)__popcll(peers);
-                    myor[d] = 0;
-                }
-                rk[j] = ((old + popc_below(peers)) << 12) | d;
-            }
-        }
+    for (int j = 0; j < ITEMS; j++)
+        if (nvalid >> j & 1u) diff |= key[j] ^ ref;
+    __syncthreads();
+    if (diff) atomicOr((unsigned long long*)&vary, (unsigned long long)diff);
+    __syncthreads();
+    const uint64_t bits_vary = vary;  // bits in which the keys differ
+    if (!bits_vary) {                 // all equal: the array is sorted
+        if (!claim) return;
+        continue;
+    }
+    const bool wfull = ballot(nvalid != (1u << items) - 1u) == 0;
+
+    for (uint32_t shift = 0; shift < 8 * KB; shift += 8) {
+        if (!(bits_vary >> shift & 0xFFu)) continue;
+        uint16_t* const myh = wh + wave * SMAX;
+        for (uint32_t i = lane; i < SMAX / 2; i += 64) ((uint32_t*)myh)[i] = 0;
+        uint32_t rp[ITEMS / 2];
+#pragma unroll
+        for (int j = 0; j < ITEMS / 2; j++) rp[j] = ~0u;
+        rank_wave<8, false>(key, nvalid, wfull, shift, 8, myh, nullptr, rp, items);
         __syncthreads();
-        for (uint32_t d = tid; d < sigma; d += NT) {
-            uint32_t run = 0;
+        uint32_t c = 0;
+        if (tid < SMAX) {
 #pragma unroll
             for (int w = 0; w < WAVES; w++) {
-                const uint32_t c = wh[w * SMAX + d];
-                wh[w * SMAX + d] = run;
-                run += c;
+                const uint32_t t = wh[w * SMAX + tid];
+                wh[w * SMAX + tid] = (uint16_t)c;
+                c += t;
             }
-            excl[d] = run;
         }
+        const uint32_t incl = wave_incl_scan(c);
+        if (lane == 63 && wave < DW) tmp[wave] = incl;
         __syncthreads();
-        block_excl_scan<NT>(excl, sigma, tmp);
-        for (uint32_t d = tid; d < sigma; d += NT) {
+        if (tid < SMAX) {
+            uint32_t ex = incl - c;
 #pragma unroll
-            for (int w = 0; w < WAVES; w++) wh[w * SMAX + d] += excl[d];
+            for (uint32_t w = 0; w < DW; w++) ex += w < wave ? tmp[w] : 0u;
+#pragma unroll
+            for (int w = 0; w < WAVES; w++) wh[w * SMAX + tid] += (uint16_t)ex;
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < ITEMS; j++) {
-            if (rk[j] != ~0u) {
-                const uint32_t d = rk[j] & 0xFFFu;
-                const uint32_t p = wh[wave * SMAX + d] + (rk[j] >> 12);
+            if (nvalid >> j & 1u) {
+                uint32_t p = j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu;
+                p += myh[(uint32_t)(key[j] >> shift) & 0xFFu];
                 lk[p] = key[j];
-                if constexpr (VB != 0) lv[p] = val[j];
+                if constexpr (VB != 0)
+                    rp[j / 2] = j & 1 ? (rp[j / 2] & 0xFFFFu) | p << 16 : (rp[j / 2] & 0xFFFF0000u) | p;
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            const uint32_t s = wave * SEG + j * 64 + lane;
-            if (s < n) {
-                key[j] = lk[s];
-                if constexpr (VB != 0) val[j] = lv[s];
-            }
+        for (int j = 0; j < ITEMS; j++)
+            if (nvalid >> j & 1u) key[j] = lk[s0 + j * 64];
+        if constexpr (VB != 0) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < ITEMS; j++)
+                if (nvalid >> j & 1u) lv[j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu] = val[j];
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < ITEMS; j++)
+                if (nvalid >> j & 1u) val[j] = lv[s0 + j * 64];
         }
-        __syncthreads();  // the OR tables of the next round overwrite lk
     }
 #pragma unroll
     for (int j = 0; j < ITEMS; j++) {
-        const uint32_t s = wave * SEG + j * 64 + lane;
-        if (s < n) {
-            kp[s] = key[j];
-            if constexpr (VB != 0) vp[s] = val[j];
+        if (nvalid >> j & 1u) {
+            kp[s0 + j * 64] = key[j];
+            if constexpr (VB != 0) vp[s0 + j * 64] = val[j];
         }
+    }
+    if (!claim) return;
     }
 }
 

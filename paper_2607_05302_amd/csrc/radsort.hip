@@ -997,6 +997,38 @@ template <int KB, int VB> struct DoOop {
     }
 };
 
+// Arrays of at most small_elems elements are sorted whole in LDS by k_sort_small, one
+// workgroup each, with no workspace.  Two shapes: 4 waves and 2048 records, of which many
+// share a compute unit, and 16 waves and the whole range.
+uint32_t small_elems(uint32_t kb, uint32_t vb) { return (kb + vb >= 12) ? 4096u : 8192u; }
+constexpr uint32_t kSmallShort = 2048;
+
+// nseg arrays by offsets_dev, or one array of n1 elements (offsets_dev null), whose call's
+// error word is err.  Both shapes run over a batch; each array falls to one of them: a
+// workgroup per array for the short ones, workgroups that claim arrays for the `longs`
+// longer ones (claim: a zeroed counter).  A lone array above 512 elements takes the large
+// shape: its lanes hold fewer items.  4096 arrays of 2^6 .. 2^13 uint32 pairs: 45 us for the
+// short ones and 105 us for the long ones; 175 us with one shape of 8 waves that gave
+// 1024 slots to the first wave before the second got any.
+template <int KB, int VB> struct DoSmall {
+    static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg, uint64_t n1,
+                   uint32_t longs, uint32_t* err, uint32_t* claim, hipStream_t s)
+    {
+        constexpr int ITEMS = KB + VB >= 12 ? 8 : 16;
+        auto* k = (typename UInt<KB>::T*)keys;
+        auto* v = (typename Payload<VB>::T*)vals;
+        const bool one = offsets_dev == nullptr;
+        if (!one || n1 <= 512)
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 4, 8>), dim3(nseg), dim3(256), 0, s, k, v,
+                               offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr);
+        if (one ? n1 > 512 : longs > 0)
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS>), dim3(one ? 1u : std::min(longs, 1024u)),
+                               dim3(512), 0, s, k, v, offsets_dev, nseg, n1,
+                               one ? 0u : kSmallShort, err, one ? nullptr : claim);
+        return RADSORT_OK;
+    }
+};
+
 int check_args(void* keys, void* payload, uint64_t n, int payload_bytes)
 {
     if (n > 0 && !keys) return RADSORT_E_INVALID;
@@ -1029,13 +1061,6 @@ int read_err(radsort_state* st, hipStream_t s, uint32_t* bits)
 // the dynamic launch form, spread over kSegLanes streams forked from the caller's
 // stream, each lane with its own workspace.
 constexpr uint32_t kSegLanes = 4;
-template <int KB, int VB> struct SmallCfg {
-    static constexpr int WAVES = 8;
-    static constexpr int ITEMS = (KB + VB >= 12) ? 8 : 16;
-    static constexpr uint32_t E = 64 * WAVES * ITEMS;
-};
-uint32_t small_elems(uint32_t kb, uint32_t vb) { return (kb + vb >= 12) ? 4096u : 8192u; }
-
 struct SegChoice {
     uint32_t b, bits;
 };
@@ -1078,7 +1103,8 @@ struct SegPlan {
     uint32_t wg_count = 0, wg_slots = 0;  // arrays of the one-workgroup path, workgroups
     uint64_t wg_off = 0, wg_slot_bytes = 0, wg_list_off = 0;
     uint64_t total = 0;
-    bool any_small = false;
+    bool any_small = false;   // arrays of k_sort_small
+    uint32_t small_long = 0;  // ... of its large shape
 };
 
 // Workgroups of the one-workgroup path (each with its own T); they never wait
@@ -1097,6 +1123,7 @@ int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb
         if (n <= 1) continue;
         if (n <= se) {
             P.any_small = true;
+            P.small_long += n > kSmallShort;
             continue;
         }
         if (n <= P.wg_hi) {
@@ -1172,19 +1199,6 @@ int lane_streams(LaneStreams** out)
     return RADSORT_OK;
 }
 
-template <int KB, int VB> struct DoSmall {
-    static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg,
-                   uint32_t* err, hipStream_t s)
-    {
-        using C = SmallCfg<KB, VB>;
-        const uint32_t nt = (8 * KB + 7) / 8;
-        hipLaunchKernelGGL((k_sort_small<KB, VB, C::WAVES, C::ITEMS>), dim3(nseg),
-                           dim3(64 * C::WAVES), 0, s, (typename UInt<KB>::T*)keys,
-                           (typename Payload<VB>::T*)vals, offsets_dev, nseg, 8u, nt, err);
-        return RADSORT_OK;
-    }
-};
-
 template <int KB, int VB> struct DoWg {
     static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg,
                    const SegPlan& P, uint8_t* ws, uint32_t* claim, uint32_t* err, hipStream_t s)
@@ -1231,6 +1245,45 @@ int run_one(void* keys, void* vals, uint64_t n, int kb, int vb, SegChoice c, uin
     if (!rc) rc = radsort_state_finalize(st, s);
     if (!rc) hipLaunchKernelGGL(k_or_error, dim3(1), dim3(64), 0, s, st->err(), errs);
     radsort_state_destroy(st);
+    return rc;
+}
+
+// One-call sorts of arrays that one workgroup sorts on chip.  The result does not depend on
+// the digits or the blocks.  A caller workspace is checked as for the other paths, and its
+// error word cleared; without one nothing is allocated, and the call waits for the stream
+// as it does where a workspace has to be freed.
+static bool sort_is_small(const Geo& g, const radsort_opts* opts)
+{
+#ifdef RS_DEBUG_ORDER
+    if (opts && (opts->flags & RADSORT_F_DEBUG_ORDER)) return false;
+#endif
+    (void)opts;
+    return g.n <= small_elems(g.kb, g.vb);
+}
+static int sort_small(void* keys, void* payload, const Geo& g, const Layout& L,
+                      const radsort_opts* opts, hipStream_t s)
+{
+    uint32_t* err = nullptr;
+    if (opts && opts->workspace) {
+        if (opts->workspace_bytes < L.total) return RADSORT_E_NOMEM;
+        err = (uint32_t*)((uint8_t*)opts->workspace + L.ctr) + g.nt;
+    }
+    const bool timing = opts && (opts->flags & RADSORT_F_TIMING);
+    if (timing) g_timer.begin();
+    g_timer.mark(kStart, 0, s);
+    int rc = dispatch<DoSmall>(g.kb, g.vb, keys, payload, (const uint64_t*)nullptr, 1u, g.n, 0u, err,
+                               (uint32_t*)nullptr, s);
+    g_timer.mark(kRoundEnd, 0, s);
+    g_timer.end();
+    g_stats.timed = 0;
+    g_stats.workspace_bytes = L.total;
+    g_stats.input_bytes = g.n * (uint64_t)(g.kb + g.vb);
+    g_stats.rounds = g.nt;
+    if (!rc) RS_HIP(hipGetLastError());
+    if (!rc && (!err || (opts->flags & RADSORT_F_CHECK))) {
+        RS_HIP(hipStreamSynchronize(s));
+        g_stats.error_bits = 0;
+    }
     return rc;
 }
 
@@ -1464,6 +1517,7 @@ int radsort_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes, int
     rc = make_geo(g, n, key_bytes, payload_bytes, digit_bits, opts);
     if (rc) return rc;
     if (n <= 1) return RADSORT_OK;
+    if (sort_is_small(g, opts)) return sort_small(keys, payload, g, make_layout(g, false, g.pack_ok), opts, (hipStream_t)stream);
     radsort_state* st = nullptr;
     rc = state_create(&st, keys, payload, n, key_bytes, payload_bytes, digit_bits, opts, true);
     if (rc) return rc;
@@ -1507,6 +1561,7 @@ int radsort_oop_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes,
     if (n <= 1) return RADSORT_OK;
     Layout L = make_layout(g, true);
     hipStream_t s = (hipStream_t)stream;
+    if (sort_is_small(g, opts)) return sort_small(keys, payload, g, L, opts, s);
     uint8_t* ws = nullptr;
     bool own = false;
     if (opts && opts->workspace) {
@@ -1655,9 +1710,9 @@ int radsort_sort_segments(void* keys, void* payload, const uint64_t* offsets,
         own = true;
     }
     // [0]: small arrays, [1 + l]: lane l, [1 + kSegLanes]: the one-workgroup path,
-    // [2 + kSegLanes]: its claim counter
+    // [2 + kSegLanes]: its claim counter, [3 + kSegLanes]: the small arrays' claim counter
     uint32_t* err_small = (uint32_t*)ws;
-    launch_fill(err_small, 3 + kSegLanes, 0, s);
+    launch_fill(err_small, 4 + kSegLanes, 0, s);
     // the lanes fork first, so that their sorts run beside the batched kernels on the
     // caller's stream; they join back at the end
     LaneStreams* L = nullptr;
@@ -1678,7 +1733,7 @@ int radsort_sort_segments(void* keys, void* payload, const uint64_t* offsets,
     }
     if (!rc && P.any_small) {
         rc = dispatch<DoSmall>(key_bytes, payload_bytes, keys, payload, offsets_dev, nseg,
-                               err_small, s);
+                               (uint64_t)0, P.small_long, err_small, err_small + 3 + kSegLanes, s);
     }
     if (!rc && P.wg_count) {
         rc = dispatch<DoWg>(key_bytes, payload_bytes, keys, payload, offsets_dev, nseg, P, ws,
@@ -1839,6 +1894,11 @@ int radsort_sort_pairs_noalloc(void* keys, void* payload, uint64_t n, int key_by
     void* ws = nullptr;
     rc = scratch_address(&ws);
     if (rc) return rc;
+    if (sort_is_small(g, &o)) {
+        o.workspace = ws;
+        o.workspace_bytes = RADSORT_NOALLOC_SCRATCH_BYTES;
+        return sort_small(keys, payload, g, L, &o, (hipStream_t)stream);
+    }
     radsort_state st;  // on the stack: nothing is allocated, on the host either
     st.g = g;
     st.L = L;

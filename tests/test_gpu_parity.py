@@ -466,3 +466,47 @@ def test_constant_digits_match_oracle(case, shared):
     assert np.array_equal(from_dev(dk, kb).astype(np.uint64), ek)
     if vb:
         assert np.array_equal(from_dev(dv, vb).astype(np.uint64), ev)
+
+
+# ---------------------------------------------------------------- arrays sorted on chip
+
+SMALL_N = [2, 63, 256, 511, 512, 513, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193]
+
+
+@pytest.mark.parametrize("kb,vb", [(4, 0), (4, 4), (4, 8), (8, 0), (8, 4), (8, 8)])
+@pytest.mark.parametrize("dist", ["uniform", "zipf", "low20", "equal"])
+def test_small_arrays_match_oracle(kb, vb, dist):
+    """One-call sorts around the sizes where the on-chip shapes begin and end, through
+    every entry point that takes them, and the same arrays as one batch."""
+    say(f"small arrays kb={kb} vb={vb} {dist}")
+    ks, vs, eks, evs = [], [], [], []
+    for n in SMALL_N:
+        keys, vals = inputs(dist, n, kb, vb, seed=11)
+        ek, ev = oracle.radsort(keys, vals, 256, kb, 1024)
+        ws = torch.empty(radsort.workspace_bytes(n, kb, vb), dtype=torch.uint8, device=DEV)
+        ws.fill_(0xA5)
+        for entry in ("sort", "workspace", "oop", "noalloc"):
+            dk, dv = to_dev(keys), to_dev(vals) if vb else None
+            if entry == "sort":
+                radsort.sort_(dk, dv, check=True)
+            elif entry == "workspace":
+                radsort.sort_(dk, dv, workspace=ws)
+                assert radsort.workspace_error(dk, dv, workspace=ws) == 0
+            elif entry == "oop":
+                radsort.oop_sort_(dk, dv)
+            else:
+                radsort.sort_noalloc_(dk, dv, check=True)
+            assert np.array_equal(from_dev(dk, kb).astype(np.uint64), ek), (entry, n)
+            if vb:
+                assert np.array_equal(from_dev(dv, vb).astype(np.uint64), ev), (entry, n)
+        ks.append(keys)
+        eks.append(ek)
+        if vb:
+            vs.append(vals)
+            evs.append(ev)
+    offsets = np.concatenate([[0], np.cumsum(SMALL_N)]).astype(np.uint64)
+    dk, dv = to_dev(np.concatenate(ks)), to_dev(np.concatenate(vs)) if vb else None
+    radsort.sort_segments_(dk, dv, offsets, tuning=None, check=True)
+    assert np.array_equal(from_dev(dk, kb).astype(np.uint64), np.concatenate(eks))
+    if vb:
+        assert np.array_equal(from_dev(dv, vb).astype(np.uint64), np.concatenate(evs))
