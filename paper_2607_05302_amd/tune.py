@@ -34,13 +34,23 @@ def table_path(key_bytes: int, payload_bytes: int) -> str:
     return os.path.join(HERE, "tuning", f"segments_k{key_bytes}_v{payload_bytes}.json")
 
 
+_tables = {}  # path -> (what the file was, its classes); read again when the file changes
+
+
 def load_table(key_bytes: int, payload_bytes: int):
     """[(max_log2n, b, digit_bits), ...] from the tuning file, or None."""
+    path = table_path(key_bytes, payload_bytes)
     try:
-        t = json.load(open(table_path(key_bytes, payload_bytes)))
+        st = os.stat(path)
+        stamp = (st.st_mtime_ns, st.st_size, st.st_ino)
+        known = _tables.get(path)
+        if known is None or known[0] != stamp:
+            with open(path) as f:
+                known = (stamp, tuple(tuple(c) for c in json.load(f)["classes"]))
+            _tables[path] = known
     except (OSError, ValueError):
         return None
-    return [tuple(c) for c in t["classes"]]
+    return list(known[1])
 
 
 def tune(key_bytes=4, payload_bytes=4, lo=14, hi=26, reps=2, seed=0x7E57, log=print):
