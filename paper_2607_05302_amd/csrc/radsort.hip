@@ -17,6 +17,7 @@
 #include "common.hpp"
 #include "kernels_state.hpp"
 #include "kernel_round.hpp"
+#include "kernel_seg.hpp"
 #include "kernel_tile.hpp"
 #include "kernels_prefix.hpp"
 #include "kernels_small.hpp"
@@ -997,6 +998,140 @@ template <int KB, int VB> struct DoOop {
     }
 };
 
+// ---- out of place in the workspace (kernel_seg.hpp) -----------------------------------------
+
+// Tile shapes of k_seg_round: 0: 2048 records, many workgroups of 4 waves to a compute unit
+// (small lone arrays: tiles for all the compute units); 1: 8192 records (4096 of 12 bytes or
+// more); 2: twice that.
+template <int KB, int VB, int SHAPE> struct SegShape {
+    static constexpr bool WIDE = KB + VB >= 12 || KB == 8;
+    static constexpr int WAVES = SHAPE == 0 ? 4 : 8;
+    static constexpr int ITEMS = SHAPE == 0 ? 8 : (WIDE ? 8 : 16) << (SHAPE - 1);
+    using Shape = RoundShape<WAVES, ITEMS, false, true, 4>;
+    static constexpr uint32_t E = 64 * WAVES * ITEMS;
+};
+uint32_t seg_tile(uint32_t kb, uint32_t vb, int shape)
+{
+    return shape == 0 ? 2048u : (kb + vb >= 12 || kb == 8 ? 4096u : 8192u) << (shape - 1);
+}
+constexpr uint64_t kSegLargeMin = 65536;  // average array of a batch for shape 2
+
+// The tables of a group of at most `arrays` arrays and `tiles` tiles, at byte offsets from a
+// 256-byte aligned base: what k_seg_clear zeroes first (hist .. ctr), then the rest.
+struct SegTables {
+    uint64_t hist, arrived, state, ctr, zero_bytes, rounds, arr, map, total;
+};
+SegTables seg_tables(uint32_t nt, uint64_t arrays, uint64_t tiles, uint64_t all_arrays,
+                     uint64_t all_tiles)
+{
+    SegTables T{};
+    uint64_t o = 0;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t at = o;
+        o = align_up(o + bytes, 256);
+        return at;
+    };
+    T.hist = take(arrays * nt * 1024);
+    T.arrived = take(arrays * 4);
+    T.state = take(tiles * 1024);
+    T.ctr = take(4 * nt);
+    T.zero_bytes = o;
+    T.rounds = take(arrays * 4);
+    T.map = take(all_tiles * 4);
+    T.arr = take(all_arrays * sizeof(SegArr));
+    T.total = o;
+    return T;
+}
+
+template <int KB, int VB>
+SegArgs<KB, VB> seg_args(void* keys, void* vals, void* sk, void* sv, uint8_t* base,
+                         const SegTables& T, uint32_t* err)
+{
+    SegArgs<KB, VB> a{};
+    a.Ak = (typename UInt<KB>::T*)keys;
+    a.Av = (typename Payload<VB>::T*)vals;
+    a.Sk = (typename UInt<KB>::T*)sk;
+    a.Sv = (typename Payload<VB>::T*)sv;
+    a.arr = (const SegArr*)(base + T.arr);
+    a.map = (const uint32_t*)(base + T.map);
+    a.hist = (uint32_t*)(base + T.hist);
+    a.arrived = (uint32_t*)(base + T.arrived);
+    a.rounds = (uint32_t*)(base + T.rounds);
+    a.state = (uint32_t*)(base + T.state);
+    a.ctr = (uint32_t*)(base + T.ctr);
+    a.err = err;
+    return a;
+}
+
+// The counting pass and the rounds of one group of `tiles` tiles.
+template <int KB, int VB, int SHAPE>
+void launch_seg_group(SegArgs<KB, VB> a, uint32_t tiles, hipStream_t s)
+{
+    using S = SegShape<KB, VB, SHAPE>;
+    SegArgs<KB, 0> h{};
+    h.Ak = a.Ak;
+    h.arr = a.arr;
+    h.map = a.map;
+    h.a0 = a.a0;
+    h.t0 = a.t0;
+    h.hist = a.hist;
+    h.arrived = a.arrived;
+    h.rounds = a.rounds;
+    h.err = a.err;
+    hipLaunchKernelGGL((k_seg_hist<KB, 512>), dim3(tiles), dim3(512), 0, s, h, S::E);
+    for (a.r = 0; a.r < (uint32_t)KB; a.r++)
+        hipLaunchKernelGGL((k_seg_round<KB, VB, typename S::Shape>), dim3(tiles),
+                           dim3(64 * S::WAVES), 0, s, a);
+}
+
+// The tile shape for one array and its tables, which `avail` bytes must hold (shape < 0: they
+// do not).  Total of the out-of-place sort, shapes 0 / 1 / 2: uint32 pairs 42 / 53 / 77 us at
+// 2^15, 47 / 55 / 78 at 2^16, - / 64 / 83 at 2^18, - / 103 / 112 at 2^21, - / 147 / 136 at 2^22, - / 394 /
+// 348 at 2^24; uint64 + uint32 77 / 81 / 110 at 2^15, 88 / 87 / 114 at 2^16, 222 / 173 / 174 at 2^20,
+// 344 / 244 / 207 at 2^21.
+struct SegOne {
+    int shape = -1;
+    SegTables T{};
+};
+SegOne seg_one(const Geo& g, uint64_t avail)
+{
+    SegOne one;
+    if (g.n >= 1ull << kSegValueBits) return one;
+    const bool wide = g.kb + g.vb >= 12 || g.kb == 8;
+    int shape = g.n <= (wide ? 1u << 16 : 1u << 18) ? 0 : g.n < (wide ? 1u << 20 : 1u << 22) ? 1 : 2;
+    for (; shape <= 2; shape++) {
+        const uint32_t E = seg_tile(g.kb, g.vb, shape);
+        const uint64_t tiles = (g.n + E - 1) / E;
+        one.T = seg_tables(g.kb, 1, tiles, 1, tiles);
+        if (one.T.total <= avail) {
+            one.shape = shape;
+            break;
+        }
+    }
+    return one;
+}
+
+// One array sorted out of place: scratch planes sk, sv and tables at base.
+template <int KB, int VB> struct DoSegOne {
+    static int run(void* keys, void* vals, uint32_t n, void* sk, void* sv, uint8_t* base,
+                   uint32_t* err, const SegOne& one, hipStream_t s)
+    {
+        const SegTables& T = one.T;
+        const int shape = one.shape;
+        SegArgs<KB, VB> a = seg_args<KB, VB>(keys, vals, sk, sv, base, T, err);
+        const uint32_t E = seg_tile(KB, VB, shape), tiles = (n + E - 1) / E;
+        // the map is all zeros too, and ends where the array's entry begins
+        const uint64_t words = T.arr / 4;
+        const uint32_t grid = (uint32_t)std::min<uint64_t>((words + 255) / 256, 4096);
+        hipLaunchKernelGGL(k_seg_clear, dim3(grid), dim3(256), 0, s, (uint32_t*)base, words,
+                           (SegArr*)(base + T.arr), n, err);
+        if (shape == 0) launch_seg_group<KB, VB, 0>(a, tiles, s);
+        else if (shape == 1) launch_seg_group<KB, VB, 1>(a, tiles, s);
+        else launch_seg_group<KB, VB, 2>(a, tiles, s);
+        return RADSORT_OK;
+    }
+};
+
 // Arrays of at most small_elems elements are sorted whole in LDS by k_sort_small, one
 // workgroup each, with no workspace.  Two shapes: 4 waves and 2048 records, of which many
 // share a compute unit, and 16 waves and the whole range.
@@ -1094,7 +1229,72 @@ uint64_t seg_wg_hi(const radsort_seg_tuning* t, uint64_t se)
     return hi;
 }
 
+// Arrays of the batch that are sorted out of place in groups (kernel_seg.hpp).
+struct SegGroups {
+    struct Group {
+        uint32_t a0, t0, t1;  // first array, tiles [t0, t1)
+    };
+    std::vector<Group> groups;
+    uint32_t count = 0, tiles = 0, G64 = 0;  // arrays, tiles, group size in 64 records
+    uint64_t hi = 0;                         // arrays of at most hi elements
+    int shape = 1;
+    SegTables T{};
+    uint64_t sk = 0, sv = 0;  // scratch planes, from the tables' base
+};
+
+// Groups for the arrays of sizes `n` (in order, all at most `top`) with `avail` bytes for scratch and tables:
+// the largest scratch whose tables fit beside it.  Arrays larger than half the scratch take
+// no part (a group is cut where the running size passes a multiple of the scratch less the
+// largest array).
+void plan_groups(SegGroups& S, const std::vector<uint32_t>& n, uint64_t top, uint32_t kb,
+                 uint32_t vb, uint64_t avail)
+{
+    const uint64_t rec = kb + vb;
+    for (uint64_t D64 = avail / (64 * rec); D64 >= 128; D64 -= D64 / 16 + 1) {
+        S.groups.clear();
+        S.count = 0;
+        uint64_t maxpad = 0, sum = 0;
+        for (uint32_t x : n) {
+            const uint64_t p = ((uint64_t)x + 63) / 64;
+            if (p > D64 / 2) continue;
+            maxpad = std::max(maxpad, p);
+            sum += x;
+            S.count++;
+        }
+        if (!S.count) return;
+        S.hi = std::min(D64 / 2 * 64, top);
+        S.shape = sum / S.count >= kSegLargeMin ? 2 : 1;
+        const uint32_t E = seg_tile(kb, vb, S.shape);
+        S.G64 = (uint32_t)(D64 - maxpad);
+        uint64_t pos = 0, group = ~0ull;
+        uint32_t arrays = 0, tiles = 0, amax = 0, tmax = 0;
+        for (uint32_t x : n) {
+            const uint64_t p = ((uint64_t)x + 63) / 64;
+            if (p > D64 / 2) continue;
+            if (pos / S.G64 != group) {
+                group = pos / S.G64;
+                S.groups.push_back({arrays, tiles, tiles});
+            }
+            arrays++;
+            tiles += (x + E - 1) / E;
+            pos += p;
+            auto& g = S.groups.back();
+            g.t1 = tiles;
+            amax = std::max(amax, arrays - g.a0);
+            tmax = std::max(tmax, g.t1 - g.t0);
+        }
+        S.tiles = tiles;
+        S.T = seg_tables(kb, amax, tmax, S.count, S.tiles);
+        S.sk = S.T.total;
+        S.sv = align_up(S.sk + D64 * 64 * kb, 256);
+        if (S.sv + D64 * 64 * vb <= avail) return;
+    }
+    S.count = 0;
+    S.groups.clear();
+}
+
 struct SegPlan {
+    SegGroups groups;
     std::vector<uint32_t> large;  // indices of the arrays that run the Radsort steps
     std::vector<uint32_t> lane;   // lane of each of them
     std::vector<SegChoice> choice;
@@ -1117,6 +1317,7 @@ int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb
     const uint32_t se = small_elems(kb, vb);
     P.wg_hi = seg_wg_hi(tuning, se);
     std::vector<std::pair<uint64_t, uint32_t>> big;
+    std::vector<uint32_t> mid;
     for (uint32_t i = 0; i < nseg; i++) {
         if (off[i + 1] < off[i]) return RADSORT_E_INVALID;
         const uint64_t n = off[i + 1] - off[i];
@@ -1128,6 +1329,7 @@ int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb
         }
         if (n <= P.wg_hi) {
             P.wg_count++;
+            mid.push_back((uint32_t)n);
             continue;
         }
         big.push_back({n, i});
@@ -1164,6 +1366,7 @@ int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb
         o = align_up(o + 4ull * P.wg_count, 256);
         P.wg_off = o;
         o += (uint64_t)P.wg_slots * P.wg_slot_bytes;
+        plan_groups(P.groups, mid, P.wg_hi, kb, vb, (uint64_t)P.wg_slots * P.wg_slot_bytes);
     }
     P.total = o;
     return RADSORT_OK;
@@ -1199,18 +1402,47 @@ int lane_streams(LaneStreams** out)
     return RADSORT_OK;
 }
 
+// The arrays of the middle path: those that fit go through the groups, the others, one
+// after the other on the same memory, through the one-workgroup kernel.
 template <int KB, int VB> struct DoWg {
     static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg,
                    const SegPlan& P, uint8_t* ws, uint32_t* claim, uint32_t* err, hipStream_t s)
     {
         using C = WgCfg<KB, VB>;
+        const SegGroups& S = P.groups;
+        uint8_t* const base = ws + P.wg_off;
+        uint64_t lo = small_elems(KB, VB);
+        if (S.count) {
+            const uint32_t E = seg_tile(KB, VB, S.shape);
+            SegArr* arr = (SegArr*)(base + S.T.arr);
+            uint32_t* map = (uint32_t*)(base + S.T.map);
+            hipLaunchKernelGGL(k_seg_plan<1024>, dim3(1), dim3(1024), 0, s, offsets_dev, nseg, lo,
+                               S.hi, S.G64, E, arr, S.count);
+            hipLaunchKernelGGL(k_seg_map, dim3(S.count), dim3(64), 0, s, (const SegArr*)arr, E,
+                               S.tiles, map);
+            SegArgs<KB, VB> a =
+                seg_args<KB, VB>(keys, vals, base + S.sk, base + S.sv, base, S.T, err);
+            for (const auto& g : S.groups) {
+                const uint64_t words = S.T.zero_bytes / 4;
+                const uint32_t grid = (uint32_t)std::min<uint64_t>((words + 255) / 256, 4096);
+                hipLaunchKernelGGL(k_seg_clear, dim3(grid), dim3(256), 0, s, (uint32_t*)base, words,
+                                   (SegArr*)nullptr, 0u, err);
+                a.a0 = g.a0;
+                a.t0 = g.t0;
+                if (S.shape == 1) launch_seg_group<KB, VB, 1>(a, g.t1 - g.t0, s);
+                else launch_seg_group<KB, VB, 2>(a, g.t1 - g.t0, s);
+            }
+            lo = std::max(lo, S.hi);
+        }
+        const uint32_t rest = P.wg_count - S.count;
+        if (!rest) return RADSORT_OK;
         uint32_t* list = (uint32_t*)(ws + P.wg_list_off);
-        hipLaunchKernelGGL(k_wg_list, dim3(1), dim3(1024), 0, s, offsets_dev, nseg,
-                           (uint64_t)small_elems(KB, VB), P.wg_hi, list, P.wg_count);
-        hipLaunchKernelGGL((k_radsort_wg<KB, VB>), dim3(P.wg_slots), dim3(C::NT), 0, s,
-                           (typename UInt<KB>::T*)keys, (typename Payload<VB>::T*)vals,
-                           offsets_dev, nseg, (const uint32_t*)list, P.wg_count, claim,
-                           ws + P.wg_off, P.wg_slot_bytes, err);
+        hipLaunchKernelGGL(k_wg_list, dim3(1), dim3(1024), 0, s, offsets_dev, nseg, lo, P.wg_hi,
+                           list, rest);
+        hipLaunchKernelGGL((k_radsort_wg<KB, VB>), dim3(std::min(rest, P.wg_slots)), dim3(C::NT), 0,
+                           s, (typename UInt<KB>::T*)keys, (typename Payload<VB>::T*)vals,
+                           offsets_dev, nseg, (const uint32_t*)list, rest, claim, base,
+                           P.wg_slot_bytes, err);
         return RADSORT_OK;
     }
 };
@@ -1259,6 +1491,28 @@ static bool sort_is_small(const Geo& g, const radsort_opts* opts)
 #endif
     (void)opts;
     return g.n <= small_elems(g.kb, g.vb);
+}
+// A one-call sort whose array fits its own workspace once more (T and the extra blocks hold
+// 3 sigma b records) runs out of place there: five launches instead of twenty.
+static SegOne sort_in_workspace_plan(const radsort_state* st)
+{
+    const Geo& g = st->g;
+    const uint64_t room = st->L.total - st->L.Tk, records = g.n * (g.kb + g.vb) + 256;
+    if (st->debug_order || records > room) return SegOne{};
+    return seg_one(g, room - records);
+}
+static int sort_in_workspace(radsort_state* st, const SegOne& one, hipStream_t s)
+{
+    const Geo& g = st->g;
+    uint8_t* const base = st->ws + st->L.Tk;
+    g_timer.mark(kStart, 0, s);
+    int rc = dispatch<DoSegOne>(g.kb, g.vb, st->keys, st->vals, (uint32_t)g.n,
+                                (void*)(base + one.T.total),
+                                (void*)(base + align_up(one.T.total + g.n * g.kb, 256)), base,
+                                st->err(), one, s);
+    g_timer.mark(kRoundEnd, 0, s);
+    if (!rc) RS_HIP(hipGetLastError());
+    return rc;
 }
 static int sort_small(void* keys, void* payload, const Geo& g, const Layout& L,
                       const radsort_opts* opts, hipStream_t s)
@@ -1530,9 +1784,14 @@ int radsort_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes, int
     hipStream_t s = (hipStream_t)stream;
     const bool timing = opts && (opts->flags & RADSORT_F_TIMING);
     if (timing) g_timer.begin();
-    rc = radsort_state_setup(st, s);
-    for (uint32_t r = 0; !rc && r < st->g.nt; r++) rc = radsort_state_round(st, s);
-    if (!rc) rc = radsort_state_finalize(st, s);
+    const SegOne one = sort_in_workspace_plan(st);
+    if (one.shape >= 0) {
+        rc = sort_in_workspace(st, one, s);
+    } else {
+        rc = radsort_state_setup(st, s);
+        for (uint32_t r = 0; !rc && r < st->g.nt; r++) rc = radsort_state_round(st, s);
+        if (!rc) rc = radsort_state_finalize(st, s);
+    }
     g_timer.end();
     g_stats.timed = 0;
     g_stats.workspace_bytes = st->L.total;
@@ -1580,7 +1839,16 @@ int radsort_oop_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes,
     // the out-of-place round runs faster in the form without co-residency (one
     // workgroup per tile) at every size and block tried, so it always takes it
     const bool dyn = true;
-    rc = dispatch<DoOop>(g.kb, g.vb, keys, payload, g, L, ws, dyn, s);
+    const SegOne one = seg_one(g, L.total - L.ring);
+    if (one.shape >= 0) {  // otherwise more tiles than look-back words
+        g_timer.mark(kStart, 0, s);
+        rc = dispatch<DoSegOne>(g.kb, g.vb, keys, payload, (uint32_t)n, (void*)(ws + L.alt_k),
+                                (void*)(ws + L.alt_v), ws + L.ring, (uint32_t*)(ws + L.ctr) + g.nt,
+                                one, s);
+        g_timer.mark(kRoundEnd, 0, s);
+    } else {
+        rc = dispatch<DoOop>(g.kb, g.vb, keys, payload, g, L, ws, dyn, s);
+    }
     g_timer.end();
     g_stats.timed = 0;
     if (!rc) {
@@ -1913,9 +2181,14 @@ int radsort_sort_pairs_noalloc(void* keys, void* payload, uint64_t n, int key_by
     st.dynamic = true;
     st.shared = true;
     hipStream_t s = (hipStream_t)stream;
-    rc = radsort_state_setup(&st, s);
-    for (uint32_t r = 0; !rc && r < st.g.nt; r++) rc = radsort_state_round(&st, s);
-    if (!rc) rc = radsort_state_finalize(&st, s);
+    const SegOne one = sort_in_workspace_plan(&st);
+    if (one.shape >= 0) {
+        rc = sort_in_workspace(&st, one, s);
+    } else {
+        rc = radsort_state_setup(&st, s);
+        for (uint32_t r = 0; !rc && r < st.g.nt; r++) rc = radsort_state_round(&st, s);
+        if (!rc) rc = radsort_state_finalize(&st, s);
+    }
     g_stats.timed = 0;
     g_stats.workspace_bytes = L.total;
     g_stats.input_bytes = n * (uint64_t)(key_bytes + payload_bytes);

@@ -510,3 +510,45 @@ def test_small_arrays_match_oracle(kb, vb, dist):
     assert np.array_equal(from_dev(dk, kb).astype(np.uint64), np.concatenate(eks))
     if vb:
         assert np.array_equal(from_dev(dv, vb).astype(np.uint64), np.concatenate(evs))
+
+
+# ---------------------------------------------------------------- out of place in the workspace
+
+# One-call sorts whose records fit their own workspace once more, at the edges of the tile
+# shapes and of the range (3 * 256 blocks of b records, less the tables), and the same
+# inputs through the out-of-place entry point.
+IN_WS = [
+    ("uniform", 8193, 4, 4, 1024),
+    ("zipf", 2048 * 5, 4, 0, 1024),
+    ("low20", (1 << 16) + 1, 8, 4, 1024),
+    ("uniform", (1 << 18) - 1, 4, 8, 1024),
+    ("uniform", (1 << 18) + 1, 4, 4, 1024),
+    ("equal", 300000, 8, 8, 1024),
+    ("sorted", 700001, 4, 4, 1024),
+    ("uniform", 768 * 1024 + 5, 4, 4, 1024),
+    ("uniform", 1 << 20, 8, 0, 2048),
+    ("few", (1 << 22) + 3, 4, 4, 8192),
+]
+
+
+@pytest.mark.parametrize("shared", [False, True], ids=["alone", "shared"])
+@pytest.mark.parametrize("case", IN_WS, ids=lambda c: "-".join(map(str, c)))
+def test_sorts_in_workspace_match_oracle(case, shared):
+    dist, n, kb, vb, b = case
+    say(f"in workspace {case} shared={shared}")
+    keys, vals = inputs(dist, n, kb, vb, seed=13)
+    ek, ev = oracle.radsort(keys, vals, 256, kb, 1024)
+    size = radsort.workspace_bytes(n, kb, vb, 8, b, shared=shared)
+    buf = torch.empty(size + 512, dtype=torch.uint8, device=DEV)
+    buf.fill_(0x5A)
+    for oop in (False, True):
+        dk, dv = to_dev(keys), to_dev(vals) if vb else None
+        if oop:
+            radsort.oop_sort_(dk, dv, block_elems=b, check=True, shared=shared)
+        else:
+            radsort.sort_(dk, dv, block_elems=b, workspace=buf[:size], shared=shared)
+            assert radsort.workspace_error(dk, dv, block_elems=b, workspace=buf[:size]) == 0
+            assert bool((buf[size:] == 0x5A).all())  # nothing past the workspace is written
+        assert np.array_equal(from_dev(dk, kb).astype(np.uint64), ek)
+        if vb:
+            assert np.array_equal(from_dev(dv, vb).astype(np.uint64), ev)

@@ -217,3 +217,28 @@ def test_segments_lanes_run_concurrently(kb):
     ek, ev = expected(offsets, keys, vals, kb)
     assert np.array_equal(dk.cpu().numpy().view(NP[kb]).astype(np.uint64), ek)
     assert np.array_equal(dv.cpu().numpy().view(np.uint32).astype(np.uint64), ev)
+
+
+@pytest.mark.parametrize("kb,vb", [(4, 0), (4, 4), (4, 8), (8, 0), (8, 4), (8, 8)])
+def test_grouped_arrays_match_oracle(kb, vb):
+    """Arrays sorted out of place in groups within the workspace: sizes around the tiles of
+    both shapes, arrays whose keys differ in an odd or even number of digits, in one digit
+    or in none, and more records than one group holds; then few arrays of which one is too
+    large for a group (it takes the one-workgroup kernel on the same memory)."""
+    say(f"grouped arrays kb={kb} vb={vb}")
+    # 52 arrays own a scratch of 52 * 65536 records: several groups
+    sizes = [8193, 8192 * 2, 8192 * 2 + 1, 16384 * 3 - 1, 16384 * 4, 4097, 12289] + [70001] * 45
+    masks = [0xFF, 0xFFFF, 0xFF00FF, 0x0, (1 << 8 * kb) - 1, 0x3 << (8 * kb - 2), 1]
+    for extra in ([], [1500000]):
+        szs = sizes[:8] + extra if extra else sizes
+        offsets, keys, vals = batch(0x6E0 + kb, szs, kb)
+        for i in range(len(szs)):
+            a, b = int(offsets[i]), int(offsets[i + 1])
+            keys[a:b] &= keys.dtype.type(masks[i % len(masks)])
+        dk = to_dev(keys)
+        dv = to_dev(vals.astype(NP[vb])) if vb else None
+        radsort.sort_segments_(dk, dv, offsets, tuning=None, check=True)
+        ek, ev = expected(offsets, keys, vals, kb)
+        assert np.array_equal(dk.cpu().numpy().view(NP[kb]).astype(np.uint64), ek)
+        if vb:
+            assert np.array_equal(dv.cpu().numpy().view(NP[vb]).astype(np.uint64), ev)
