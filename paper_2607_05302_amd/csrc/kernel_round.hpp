@@ -98,6 +98,8 @@ struct TileArgs {
     uint32_t* done;          // [2^ring_log2]: tile + 1 once done, zeroed per round
     const uint32_t* stbase;  // [super-tile][sigma]: digit counts before each super-tile,
     const uint32_t* stsum;   // from the start of its chunk: [chunk][sigma], the rest
+    uint32_t* rows;          // k_tile_round with kChainRows: look-back words [tile][sigma], zero
+    uint64_t* ring64;        // ... with kChainRing: [2^(ring_log2 - 1)][sigma], zero on entry
     uint32_t* err;
     uint32_t* tile_ctr;      // dynamic launches: next tile to claim, zero on entry
     uint32_t shift, bits, log2b, npi, ring_log2;

@@ -1,6 +1,6 @@
 // The Radsort round (Alg. 5) in the default draw order for digits of at most 8
 // bits: the protocol of kernel_round.hpp (tiles, super-tile look-back, ring, pool
-// draws, the GPU form of Lemma 1: see there), arranged so that two workgroups with
+// draws, the GPU form of Lemma 1: see there; one-call sorts: CHAIN below), arranged so that two workgroups with
 // large tiles share a compute unit.
 //
 // What bounds it: a tile is a chain of dependent steps (claim, block table, loads,
@@ -130,7 +130,33 @@ __device__ __forceinline__ void rank_wave(const K (&key)[ITEMS], uint32_t nvalid
     }
 }
 
-template <int KB, int VB, int FB, class SH>
+// CHAIN: how a tile finds its digit starts.
+//  kChainNone: the counting pass before the round gives those of its super-tile, and it adds
+//    the counts of the super-tile's earlier tiles (rounds planned one at a time).
+// One-call sorts plan all rounds ahead (k_hist_plan) and run no counting pass; a tile looks
+// back over all earlier tiles, each of which publishes its counts and then its counts up to
+// and including itself:
+//  kChainRows: a word of its own for every (tile, digit), 0 until published; n < 2^30;
+//  kChainRing: 64-bit words in a ring, tagged with their tile.  Tile T takes the slot of
+//    T - W (W slots) once T - W and T - W + 1 are done: then T - W writes it no more, and a
+//    reader that still wants its word starts its look-back again and meets the inclusive
+//    count of T - W + 1, or a later one, first.
+// A finished look-back over all earlier tiles also says that all of them have published
+// their counts, hence that their loads have returned: the tile's draws wait for nothing
+// more.  Measured without and with, whole sorts: 7.39 -> 6.47 ms at 2^28 uint32 pairs,
+// 13.8 -> 12.6 ms at 2^28 skewed uint64, 5.93 -> 4.82 ms at 2^26 uint64+uint32 (a counting
+// pass reads the keys and their block table again each round: 270, 429 and 157 us); rows:
+// 0.81 -> 0.75 ms at 2^24 uint32 pairs, 0.42 -> 0.34 ms at 2^20 uint64+uint32.
+constexpr int kChainNone = 0, kChainRows = 1, kChainRing = 2;
+constexpr uint32_t kRowAgg = 1u << 30, kRowIncl = 2u << 30, kRowValue = kRowAgg - 1;
+constexpr uint64_t kRingAgg = 1ull << 62, kRingIncl = 2ull << 62;
+// status | tile + 1 (30 bits) | value
+__device__ __forceinline__ uint64_t ring_word(uint64_t status, uint32_t tile, uint32_t value)
+{
+    return status | (uint64_t)(tile + 1) << 32 | value;
+}
+
+template <int KB, int VB, int FB, class SH, int CHAIN>
 __global__ __launch_bounds__(SH::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB> a)
 {
@@ -150,8 +176,11 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     // uint64 keys of 4096 skewed values 0.743 and 0.572 ms.
     constexpr bool OR_RANK = KB == 4 && VB <= 4;
     constexpr int SCH = 4;  // items of a loop scheduled together (bounds the registers)
-    // predecessors read per look-back step (a super-tile has 2^16 slots or one block)
-    constexpr int LBW = E >= 16384 ? 4 : 8;
+    // Predecessors read per look-back step.  Ring words cost traffic: at 2^28 uint32 pairs a
+    // round took 1238, 1288, 1336 and 1358 us with 1, 2, 4 and 8 of them; keys alone have
+    // shorter tiles, so longer look-backs: 889, 875, 880 and 904 us at 2^28 uint32.
+    constexpr int LBW = CHAIN == kChainRing ? (VB ? 1 : 2)
+                        : CHAIN == kChainRows || E < 16384 ? 8 : 4;
     static_assert(SMAX <= NT, "one digit per thread");
     static_assert((E & (E - 1)) == 0 && E <= 32768, "16-bit positions, 0xFFFF unused");
     static_assert(MAXBLK >= 1 && MAXBLK <= NT, "one thread per block of a tile");
@@ -179,8 +208,8 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     const uint64_t wmask = (1ull << wlog) - 1;
     const uint32_t mst = 1u << a.st_log2;  // tiles per super-tile
 
-    bool packed = a.pack_est != nullptr;
-    if (a.mode) {
+    bool packed = false;
+    if constexpr (CHAIN != kChainNone) {
         const uint32_t m = *a.mode;
         if (m == kModeSkip) return;  // the round's digit is the same for every element
         packed = m == kModePacked;
@@ -253,15 +282,21 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     uint32_t Sd = 0, sbase = 0, poff = 0;
     if (d < sigma) {
         Sd = a.S[d];
-        sbase = super_start(a, tile >> a.st_log2, sigma, d);
+        if constexpr (CHAIN == kChainNone) sbase = super_start(a, tile >> a.st_log2, sigma, d);
         if (packed) poff = a.pack_est[d] & (b - 1);  // the packed round's offset
     }
     // reuse of this tile's ring slot: the done words of the tiles that must have
     // finished, requested now and checked before the counts are published
     uint32_t rq = 0, rqend = 0, rv = 0;
-    if ((uint64_t)tile > wmask) {
-        rq = tile - (uint32_t)wmask - 1;              // tile - W
-        rqend = min((rq | (mst - 1)) + 1, ntiles);    // end of its super-tile
+    const uint32_t W64 = 1u << (wlog - 1);  // kChainRing's slots
+    if (CHAIN == kChainRing ? tile >= W64 : CHAIN == kChainNone && (uint64_t)tile > wmask) {
+        if constexpr (CHAIN == kChainRing) {
+            rq = tile - W64;
+            rqend = rq + 2;
+        } else {
+            rq = tile - (uint32_t)wmask - 1;            // tile - W
+            rqend = min((rq | (mst - 1)) + 1, ntiles);  // end of its super-tile
+        }
         if (rq + tid < rqend) rv = ld_agent(a.done + ((rq + tid) & wmask));
     }
 
@@ -315,7 +350,12 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (mst > 1)  // a super-tile of one tile has no look-back
+        if constexpr (CHAIN == kChainRows)
+            st_agent(a.rows + (uint64_t)tile * sigma + d, c | (tile ? kRowAgg : kRowIncl));
+        else if constexpr (CHAIN == kChainRing)
+            st_agent(a.ring64 + (uint64_t)(tile & (W64 - 1)) * sigma + d,
+                     ring_word(tile ? kRingAgg : kRingIncl, tile, c));
+        else if (mst > 1)  // a super-tile of one tile has no look-back
             st_agent(a.agg + (uint64_t)(tile & wmask) * sigma + d, c | epoch_bit(tile, wlog));
     }
     const uint32_t cincl = wave_incl_scan(c);
@@ -339,7 +379,61 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
 
     // ---- look back over the super-tile -------------------------------------------------
     uint32_t bs = sbase + poff;  // digit-d elements before the tile (from the block starts)
-    if (d < sigma) {
+    if constexpr (CHAIN != kChainNone) {
+        if (d < sigma) {
+            using Wd = typename std::conditional<CHAIN == kChainRows, uint32_t, uint64_t>::type;
+            auto word = [&](uint32_t t) -> Wd* {
+                if constexpr (CHAIN == kChainRows) return a.rows + (uint64_t)t * sigma + d;
+                else return a.ring64 + (uint64_t)(t & (W64 - 1)) * sigma + d;
+            };
+            uint32_t k = tile, spins = 0, acc = 0;
+            bool stalled = false;
+            while (k > 0) {
+                const uint32_t m = stalled ? 1u : min<uint32_t>(LBW, k);
+                Wd w[LBW];
+#pragma unroll
+                for (int i = 0; i < LBW; i++)
+                    if ((uint32_t)i < m) w[i] = ld_agent(word(k - 1 - i));
+                uint32_t used = 0;
+                bool ready = true, found = false, again = false;
+#pragma unroll
+                for (int i = 0; i < LBW; i++) {
+                    if ((uint32_t)i < m && ready && !found) {
+                        if constexpr (CHAIN == kChainRows) {
+                            ready = w[i] != 0;
+                            found = w[i] >= kRowIncl;
+                            if (ready) acc += w[i] & kRowValue;
+                        } else {
+                            const uint32_t tag = (uint32_t)(w[i] >> 32) & 0x3FFFFFFFu;
+                            ready = tag == k - i;            // tile k - 1 - i
+                            again = tag > k - i;             // its slot was taken over
+                            found = ready && w[i] >= kRingIncl;
+                            if (ready) acc += (uint32_t)w[i];
+                        }
+                        if (ready) used = i + 1;
+                    }
+                }
+                k -= used;
+                if (found) break;
+                if (again) {
+                    k = tile;
+                    acc = 0;
+                }
+                stalled = !ready && used == 0 && !again;
+                if (!ready) {
+                    if (spin_give_up(++spins, a.err)) break;
+                    spin_pause();
+                }
+            }
+            if constexpr (CHAIN == kChainRows) {
+                if (tile) st_agent(word(tile), (acc + c) | kRowIncl);
+            } else {
+                if (tile) st_agent(word(tile), ring_word(kRingIncl, tile, acc + c));
+                __builtin_amdgcn_s_waitcnt(0);  // before the tile is done (ring reuse)
+            }
+            bs += acc;
+        }
+    } else if (d < sigma) {
         // the counts of tiles st0 .. tile-1, up to LBW loads at once; while
         // one has not published, poll that one alone
         uint32_t k = tile, spins = 0;
@@ -406,7 +500,7 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     const uint32_t fw = nfill | nwrite << 16, fwincl = wave_incl_scan(fw);
     const uint32_t qsum = wave_sum(d < sigma ? q0 : 0u);
     __syncthreads();  // tmp was read; the look-back of every digit is done
-    if (tid == 0) st_agent(a.done + (tile & wmask), tile + 1);
+    if (CHAIN != kChainRows && tid == 0) st_agent(a.done + (tile & wmask), tile + 1);
     if (lane == 63 && wave < DW) {
         tmp[wave] = qsum;
         tmp[DW + wave] = fwincl;
@@ -434,17 +528,14 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     };
     uint32_t pv = 0;
     if (tid < nfills) pv = pool_entry(F + tid);
-    // input blocks (counted from the round's first) among the drawn entries
-    const uint32_t in_lo = packed ? (F > sigma ? F - sigma : 0u) : F;
-    const uint32_t in_hi = packed ? (F + nfills > sigma ? F + nfills - sigma : 0u) : F + nfills;
     // The drawn blocks of this super-tile were loaded before their tiles' counts, which
     // the look-back read; for earlier tiles wait until they are done.  The wait ends
     // before the draws are published: later tiles that continue a drawn block write
     // into it as soon as they see its entry in pi_new.
-    if (in_hi > in_lo) {
-        const uint32_t olo = (uint32_t)(((uint64_t)in_lo << log2b) / E);
+    if (CHAIN == kChainNone && nfills) {
+        const uint32_t olo = (uint32_t)(((uint64_t)F << log2b) / E);
         const uint32_t ohi =
-            min<uint32_t>((uint32_t)((((uint64_t)in_hi << log2b) - 1) / E) + 1, st0);
+            min<uint32_t>((uint32_t)((((uint64_t)(F + nfills) << log2b) - 1) / E) + 1, st0);
         for (uint32_t o = olo + tid; o < ohi; o += NT) {
             const uint32_t* w = a.done + (o & wmask);
             uint32_t v = ld_agent(w), spins = 0;

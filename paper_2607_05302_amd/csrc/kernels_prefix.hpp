@@ -94,38 +94,23 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
     const uint32_t* __restrict__ f_in_p, uint64_t n, uint32_t shift, uint32_t bits,
     uint32_t log2b, uint32_t npi, uint32_t sts_log2, uint32_t* __restrict__ cnt,
     uint32_t* __restrict__ csum, uint32_t* err, uint32_t* __restrict__ done, uint32_t plan,
-    PlanPtrs pp, RoundModes rm)
+    PlanPtrs pp)
 {
     using K = typename UInt<KB>::T;
     constexpr uint32_t NW = NT / 64;
     constexpr int U = 16;  // loads in flight per thread
     __shared__ uint32_t h[kHistWords];
     __shared__ uint32_t bphys[OOP ? 1 : kMaxSuperBlocks], blen_s[OOP ? 1 : kMaxSuperBlocks];
-    __shared__ uint32_t last, mode_s;
-    __shared__ uint64_t vary_s;
+    __shared__ uint32_t last;
     const uint32_t sigma = 1u << bits, dmask = sigma - 1, two_sigma = 2 * sigma;
     const uint32_t clog = min(kCopiesLog2, kHistLog2 - bits), copies = 1u << clog;
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    uint32_t mode = plan == 3 ? kModePacked : kModeRun;
-    if (rm.vary && rm.r) {  // round 0 decides once its keys are read
-        mode = round_mode(*rm.vary, rm.r, rm.nt, bits);
-        if (mode == kModeSkip) {
-            if (blockIdx.x == 0 && tid == 0) rm.mode[rm.r] = mode;
-            return;
-        }
-    }
     uint32_t* const mine = h + (lane & (copies - 1));
     for (uint32_t i = tid; i < copies * sigma; i += NT) h[i] = 0;
-    if (tid == 0) vary_s = 0;
 
     const uint64_t s0 = (uint64_t)blockIdx.x << sts_log2, span = 1ull << sts_log2;
     const uint32_t b = 1u << log2b;
-    const K ref = rm.vary && !rm.r ? Ak[0] : (K)0;
-    K diff = 0;  // bits in which this thread's keys differ from the array's first
-    auto add = [&](K x) {
-        atomicAdd(mine + (((uint32_t)(x >> shift) & dmask) << clog), 1u);
-        diff |= x ^ ref;
-    };
+    auto add = [&](K x) { atomicAdd(mine + (((uint32_t)(x >> shift) & dmask) << clog), 1u); };
     if constexpr (OOP) {
         __syncthreads();
         const uint64_t s1 = min<uint64_t>(n, s0 + span);
@@ -195,16 +180,12 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
                 if ((uint32_t)j * 64 < 1u << plog && o0 + j * 64 + lane < len) add(x[j]);
         }
     }
-    if (rm.vary && !rm.r && diff)
-        atomicOr((unsigned long long*)&vary_s, (unsigned long long)diff);
     __syncthreads();
     for (uint32_t d = tid; d < sigma; d += NT) {
         uint32_t s = 0;  // the copies from a start of this thread's own (banks)
         for (uint32_t c = 0; c < copies; c++) s += h[(d << clog) + ((c + d) & (copies - 1))];
         st_agent(cnt + (uint64_t)blockIdx.x * sigma + d, s);
     }
-    if (rm.vary && !rm.r && tid == 0 && vary_s)
-        __hip_atomic_fetch_or(rm.vary, vary_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // The rows pass between workgroups by agent-scope stores and loads: each thread waits
     // until its stores are done (a barrier waits for none of them), then one thread counts
     // the workgroup in.  (An agent-scope release fence here writes back the whole L2 in
@@ -222,26 +203,110 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
     const uint32_t chunks = (gridDim.x + kScanRows - 1) / kScanRows;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) {
-        last = add_agent(done, 1u) == chunks - 1;
-        if (last && rm.vary) {
-            if (!rm.r)
-                mode = round_mode(__hip_atomic_load(rm.vary, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT),
-                                  0, rm.nt, bits);
-            rm.mode[rm.r] = mode;
-        }
-        mode_s = mode;
-    }
+    if (tid == 0) last = add_agent(done, 1u) == chunks - 1;
     __syncthreads();
     if (!last) return;
     scan_columns<NT>(csum, chunks, sigma, part, cnt + (uint64_t)(gridDim.x - 1) * sigma);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();  // the totals row is written by this workgroup; h is free
-    const bool packed = mode_s == kModePacked;
+    const bool packed = plan == 3;
     plan_round<NT>(cnt + (uint64_t)(gridDim.x - 1) * sigma, sigma, log2b, h, h + sigma,
                    h + 2 * sigma, pp.S, pp.Pidx, pp.Plen, pp.f,
                    packed || plan == 2 ? pp.est : nullptr, packed);
+}
+
+// The plans of all rounds of a one-call sort at once: the digit counts of every key
+// position (which do not depend on the order of the elements) added up in est, zero on entry,
+// by one pass over the keys; the last workgroup (counter *arrived, zero on entry) turns them
+// into S, P, f and est of every round and the rounds' modes, one wave per round.  Counts by
+// lane copies as in k_supertile_counts.  sigma <= 256.
+// Bound by the read of the keys while a key has four digits: 0.27 ms at 2^28 uint32
+// (4.0 TB/s), where counting before each round took 4 x 0.27 ms; 0.50 ms at 2^28 uint64
+// (4.3 TB/s) against 8 x 0.43 ms.
+constexpr uint32_t kPlanWords = 16384;  // LDS words of counts
+template <int KB, int FB, int NT>
+__global__ __launch_bounds__(NT) void k_hist_plan(const typename UInt<KB>::T* __restrict__ keys,
+                                                  uint64_t n, uint32_t bits_, uint32_t nt_,
+                                                  uint32_t log2b, uint32_t per_wg, PlanPtrs p,
+                                                  uint32_t* __restrict__ mode,
+                                                  uint32_t* __restrict__ arrived)
+{
+    using K = typename UInt<KB>::T;
+    constexpr int U = 8;
+    constexpr uint32_t NW = NT / 64;
+    __shared__ uint32_t h[kPlanWords], last, vary[2];
+    const uint32_t bits = FB ? (uint32_t)FB : bits_, nt = FB ? (8u * KB + FB - 1) / (FB ? FB : 1) : nt_;
+    const uint32_t sigma = 1u << bits, dmask = sigma - 1, words = nt * sigma;
+    uint32_t clog = 0;  // copies: 16 (8 for 64-bit keys), fewer where few keys are counted
+    while (clog < kCopiesLog2 && (words << (clog + 1)) <= min(kPlanWords, per_wg / 4)) clog++;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (uint32_t i = tid; i < words << clog; i += NT) h[i] = 0;
+    if (tid < 2) vary[tid] = 0;
+    __syncthreads();
+    uint32_t* const mine = h + (lane & ((1u << clog) - 1));
+    const uint64_t c0 = (uint64_t)blockIdx.x * per_wg, c1 = min<uint64_t>(n, c0 + per_wg);
+    for (uint64_t c = c0; c < c1; c += NT * U) {
+        K x[U];
+#pragma unroll
+        for (int j = 0; j < U; j++) x[j] = keys[min<uint64_t>(c + j * NT + tid, c1 - 1)];
+#pragma unroll
+        for (int j = 0; j < U; j++) {
+            if (c + j * NT + tid < c1)
+#pragma unroll
+                for (uint32_t r = 0; r < nt; r++)
+                    atomicAdd(mine + ((r * sigma + ((uint32_t)(x[j] >> (bits * r)) & dmask)) << clog),
+                              1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < words; i += NT) {
+        uint32_t s = 0;
+        for (uint32_t c = 0; c < 1u << clog; c++) s += h[(i << clog) + c];
+        if (s) add_agent(p.est + i, s);
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's additions are done
+    __syncthreads();
+    if (tid == 0) last = add_agent(arrived, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    // the rounds whose digit varies (bit r of vary)
+    uint32_t* const cnt = h;  // the totals
+    for (uint32_t i = tid; i < words; i += NT) cnt[i] = ld_agent(p.est + i);
+    __syncthreads();
+    for (uint32_t r = wave; r < nt; r += NW) {
+        bool all = false;
+        for (uint32_t d = lane; d < sigma; d += 64) all |= cnt[r * sigma + d] == n;
+        if (ballot(all) == 0 && lane == 0) atomicOr(&vary[r >> 5], 1u << (r & 31));
+    }
+    __syncthreads();
+    const uint64_t v = (uint64_t)vary[1] << 32 | vary[0];
+    const uint32_t top = v ? 63u - (uint32_t)__builtin_clzll(v) : nt - 1;
+    const uint32_t b = 1u << log2b;
+    for (uint32_t r = wave; r < nt; r += NW) {
+        const bool packed = r == top;
+        uint32_t elems = 0, blocks = 0;  // before this group of 64 digits
+        for (uint32_t d0 = 0; d0 < sigma; d0 += 64) {
+            const uint32_t d = d0 + lane;
+            const bool in = d < sigma;
+            const uint32_t c = in ? cnt[r * sigma + d] : 0u;
+            const uint32_t ei = wave_incl_scan(c), es = elems + ei - c;
+            const uint32_t span = c + (packed ? es & (b - 1) : 0u);
+            const uint32_t C = in ? 1 + (span >> log2b) : 0u;
+            const uint32_t bi = wave_incl_scan(C), s = sigma + blocks + bi - C;
+            if (in) {
+                p.S[r * sigma + d] = s;
+                p.Pidx[(r + 1) * sigma + d] = s + C - 1;
+                p.Plen[(r + 1) * sigma + d] = span & (b - 1);
+                p.est[r * sigma + d] = es;
+            }
+            elems += (uint32_t)__builtin_amdgcn_readlane((int)ei, 63);
+            blocks += (uint32_t)__builtin_amdgcn_readlane((int)bi, 63);
+        }
+        if (lane == 0) {
+            p.f[r + 1] = sigma + blocks;
+            mode[r] = packed ? kModePacked : v >> r & 1u ? kModeRun : kModeSkip;
+        }
+    }
 }
 
 }  // namespace rs

@@ -142,21 +142,8 @@ __device__ void plan_round(const uint32_t* __restrict__ cnt, uint32_t sigma, uin
 // digit is the same for every element would leave the logical sequence as it is and is
 // left out; the last of the others is packed (plan_round); the rounds after it are left
 // out too.  When no digit varies the last round runs, packed, so that finalize finds a
-// packed state.  vary: the bits in which any two keys differ, ORed together by round 0's
-// counting pass, which reads every key anyway.
+// packed state.  k_hist_plan sets them.
 constexpr uint32_t kModeRun = 0, kModeSkip = 1, kModePacked = 2;
-struct RoundModes {
-    uint64_t* vary;   // null: every round runs, packed as the host says
-    uint32_t* mode;   // [n_t]
-    uint32_t r, nt;
-};
-__device__ __forceinline__ uint32_t round_mode(uint64_t vary, uint32_t r, uint32_t nt,
-                                               uint32_t bits)
-{
-    const uint32_t last = vary ? (63u - (uint32_t)__builtin_clzll(vary)) / bits : nt - 1;
-    if (r == last) return kModePacked;
-    return (vary >> (bits * r)) & ((1ull << bits) - 1) ? kModeRun : kModeSkip;
-}
 
 // setup (Alg. 4): pi = [0..sigma) | 2 sigma .. sigma + f - 2 | sigma .. 2 sigma),
 // the n mod b tail of A copied to physical block sigma, the other pi buffer
@@ -285,7 +272,7 @@ __global__ void k_pack_fixup(const uint32_t* __restrict__ pi_old, uint32_t* __re
 }
 
 // The fixup of a round: by its mode in a one-call sort (mode not null), else the plain
-// one.  A round that was left out hands pi, P, f (and S and est, which finalize reads of
+// one.  A round that was left out (its look-back words are still clear) hands pi, P, f (and S and est, which finalize reads of
 // the last index) on as they are.  Index 0 of S, est, Pidx, Plen and f is the round's own.
 __global__ void k_fixup(uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi_new,
                         PlanPtrs p, uint32_t* __restrict__ blen, uint64_t* __restrict__ opened,
@@ -314,9 +301,6 @@ __global__ void k_fixup(uint32_t* __restrict__ pi_old, uint32_t* __restrict__ pi
             }
         }
         if (j0 == 0) p.f[1] = p.f[0];
-        // round 0 was counted before it was left out
-        for (uint64_t i = j0; !r && i < ring_words; i += (uint64_t)gridDim.x * blockDim.x)
-            ring[i] = 0;
     }
 }
 

@@ -478,10 +478,16 @@ struct radsort_state {
         return PlanPtrs{u32(L.S), u32(L.Pidx), u32(L.Plen), u32(L.f), u32(L.est)};
     }
     uint32_t* err() const { return u32(L.ctr) + g.nt; }
-    // one-call sorts on the tile kernel decide each round's mode on the device: mode
-    // words 0 .. n_t - 1 of the counters, the 64-bit `vary` word past the error word
+    // one-call sorts on the tile kernel: all rounds are planned ahead from one count of all
+    // key positions (k_hist_plan; mode words 0 .. n_t - 1 of the counters), and tiles look
+    // back over all earlier tiles, not over a counted super-tile's
     bool modes() const { return pack && g.tile && msd_shift < 0; }
-    uint64_t* vary() const { return (uint64_t*)(u32(L.ctr) + ((g.nt + 3) & ~1u)); }
+    // a look-back word per (tile, digit) in the place of the ring and the digit starts
+    // where they fit (st_log2), else a ring of them in the place of the ring; they are
+    // zeroed per round
+    bool chain_rows() const { return modes() && g.st_log2 == 0 && g.n <= kRowValue; }
+    uint64_t zero_from() const { return chain_rows() ? L.stcnt : L.zero; }
+    uint64_t zero_words() const { return (L.zero + L.zero_bytes - zero_from()) / 4; }
     // entries of pi: a packed round's extra blocks too
     uint32_t npx() const { return g.npi + (pack ? g.sigma : 0u); }
 };
@@ -548,7 +554,7 @@ void launch_super_counts(const Geo& g, const typename UInt<KB>::T* Ak,
                          const typename UInt<KB>::T* Tk, const uint32_t* pi,
                          const uint32_t* blen, const uint32_t* f_in, uint32_t shift,
                          uint32_t* stcnt, uint32_t* csum, uint32_t* err, uint32_t* done_ctr,
-                         uint32_t r, PlanPtrs p, hipStream_t s, bool packed, RoundModes rm)
+                         uint32_t r, PlanPtrs p, hipStream_t s, bool packed)
 {
     const uint32_t rows = (OOP ? g.oop_supers : g.supers) + 1;
     const uint32_t sts_log2 = OOP ? g.oop_st_log2 + (uint32_t)ilog2(g.oop_E)
@@ -561,8 +567,7 @@ void launch_super_counts(const Geo& g, const typename UInt<KB>::T* Ak,
     // 162 rows: 17.5 against 15.5 us)
     auto launch = [&](auto kern, uint32_t threads) {
         hipLaunchKernelGGL(kern, dim3(rows), dim3(threads), 0, s, Ak, Tk, pi, blen, f_in, g.n, shift,
-                           g.bits, g.log2b, g.npi, sts_log2, stcnt, csum, err, done_ctr, plan, pr,
-                           rm);
+                           g.bits, g.log2b, g.npi, sts_log2, stcnt, csum, err, done_ctr, plan, pr);
     };
     if (rows <= 256) launch(k_supertile_counts<KB, OOP, 1024>, 1024);
     else launch(k_supertile_counts<KB, OOP, 512>, 512);
@@ -604,12 +609,18 @@ int launch_round_t(const Geo& g, TileArgs<KB, VB>& a, hipStream_t s, bool dyn = 
         if (g.tile && !seq) {
             using TL = TileShape<KB, VB, true>;
             using TS = TileShape<KB, VB, false>;
-            const void* kern =
-                g.tile_large
-                    ? (g.bits == 8 ? (const void*)&k_tile_round<KB, VB, 8, typename TL::Shape>
-                                   : (const void*)&k_tile_round<KB, VB, 0, typename TL::Shape>)
-                    : (g.bits == 8 ? (const void*)&k_tile_round<KB, VB, 8, typename TS::Shape>
-                                   : (const void*)&k_tile_round<KB, VB, 0, typename TS::Shape>);
+            auto pick = [&](auto chain) {
+                constexpr int CH = decltype(chain)::value;
+                if (g.tile_large)
+                    return g.bits == 8
+                               ? (const void*)&k_tile_round<KB, VB, 8, typename TL::Shape, CH>
+                               : (const void*)&k_tile_round<KB, VB, 0, typename TL::Shape, CH>;
+                return g.bits == 8 ? (const void*)&k_tile_round<KB, VB, 8, typename TS::Shape, CH>
+                                   : (const void*)&k_tile_round<KB, VB, 0, typename TS::Shape, CH>;
+            };
+            const void* kern = a.rows     ? pick(std::integral_constant<int, kChainRows>{})
+                               : a.ring64 ? pick(std::integral_constant<int, kChainRing>{})
+                                          : pick(std::integral_constant<int, kChainNone>{});
             return launch_dynamic(kern, tiles, 64 * (g.tile_large ? TL::WAVES : TS::WAVES), a, s,
                                   false);
         }
@@ -670,15 +681,25 @@ template <int KB, int VB> struct Ops {
         const Geo& g = st->g;
         g_timer.mark(kStart, 0, s);
         // every round is planned later from its own digit counts
-        launch_fill(st->u32(st->L.ctr), g.nt + 8, 0, s);
+        const uint64_t from = st->modes() ? st->L.est : st->L.ctr;  // est, then the counters
+        launch_fill(st->u32(from), (st->L.ctr - from) / 4 + g.nt + 8, 0, s);
         uint64_t work = std::max<uint64_t>(st->npx(), g.n & (g.b - 1));
         uint32_t grid = (uint32_t)std::min<uint64_t>((work + 255) / 256, 4096);
         hipLaunchKernelGGL((k_setup<KB, VB>), dim3(grid), dim3(256), 0, s, (K*)st->keys,
                            (V*)st->vals, (K*)(st->ws + st->L.Tk), (V*)(st->ws + st->L.Tv), g.n,
                            g.log2b, g.sigma, g.npi, st->npx(), st->pi(0), st->pi(1), st->u32(st->L.blen),
                            (uint64_t*)(st->ws + st->L.opened), st->u32(st->L.Pidx),
-                           st->u32(st->L.Plen), st->u32(st->L.f), st->u32(st->L.zero),
-                           st->L.zero_bytes / 4);
+                           st->u32(st->L.Plen), st->u32(st->L.f), st->u32(st->zero_from()),
+                           st->zero_words());
+        if (st->modes()) {
+            // 16384 keys to a workgroup, more where that makes over 2048 workgroups
+            const uint64_t per = align_up(std::max<uint64_t>(16384, (g.n + 2047) / 2048), 8192);
+            const dim3 grid((uint32_t)((g.n + per - 1) / per));
+            auto* kern = g.bits == 8 ? k_hist_plan<KB, 8, 1024> : k_hist_plan<KB, 0, 1024>;
+            hipLaunchKernelGGL(kern, grid, dim3(1024), 0, s, (const K*)st->keys, g.n, g.bits, g.nt,
+                               g.log2b, (uint32_t)per, st->plan(), st->u32(st->L.ctr),
+                               st->err() + 1);
+        }
         g_timer.mark(kSetupEnd, 0, s);
         st->cur = 0;
         st->rounds_done = 0;
@@ -769,11 +790,9 @@ template <int KB, int VB> struct Ops {
             a.Xk = (K*)(st->ws + st->L.Xk);
             a.Xv = (V*)(st->ws + st->L.Xv);
         }
-        RoundModes rm{};
-        if (modes) {
-            a.mode = st->u32(st->L.ctr) + r;
-            rm = RoundModes{st->vary(), st->u32(st->L.ctr), r, g.nt};
-        }
+        if (modes) a.mode = st->u32(st->L.ctr) + r;
+        if (st->chain_rows()) a.rows = (uint32_t*)(st->ws + st->L.stcnt);
+        else if (modes) a.ring64 = (uint64_t*)(st->ws + st->L.agg);
 #ifdef RS_TIMELINE
         a.tl = g.tiles <= g_tl_tiles ? g_tl : nullptr;
 #endif
@@ -787,9 +806,10 @@ template <int KB, int VB> struct Ops {
         a.stsum = st->u32(st->L.csum);
         // the ring is clear: setup or the previous round's fixup cleared it
         g_timer.mark(kCountBegin, r, s);
-        launch_super_counts<KB, false>(g, a.Ak, a.Tk, a.pi_old, a.blen, a.f_in, a.shift, stcnt,
+        if (!modes)
+            launch_super_counts<KB, false>(g, a.Ak, a.Tk, a.pi_old, a.blen, a.f_in, a.shift, stcnt,
                                        st->u32(st->L.csum), a.err, a.tile_ctr + 1, r,
-                                       st->plan(), s, packed, rm);
+                                       st->plan(), s, packed);
         g_timer.mark(kRoundBegin, r, s);
         int rc = launch_round_t<KB, VB, false>(g, a, s, st->dynamic, st->seq_draws);
         if (rc) return rc;
@@ -804,7 +824,7 @@ template <int KB, int VB> struct Ops {
         else
             hipLaunchKernelGGL(k_fixup, dim3(grid), dim3(256), 0, s, st->pi(st->cur),
                                st->pi(st->cur ^ 1), p, st->u32(st->L.blen), a.opened, g.sigma,
-                               g.log2b, g.npi, a.npi_x, st->u32(st->L.zero), st->L.zero_bytes / 4,
+                               g.log2b, g.npi, a.npi_x, st->u32(st->zero_from()), st->zero_words(),
                                a.mode, r);
         g_timer.mark(kFixupEnd, r, s);
         st->cur ^= 1;
@@ -929,7 +949,7 @@ template <int KB, int VB> struct Ops {
             g_timer.mark(kCountBegin, r, s);
             launch_super_counts<KB, true>(g, a.Ak, (const K*)nullptr, nullptr, nullptr, nullptr,
                                           a.shift, stcnt, (uint32_t*)(ws + L.csum), a.err,
-                                          a.tile_ctr + 1, r, p, s, false, RoundModes{});
+                                          a.tile_ctr + 1, r, p, s, false);
             g_timer.mark(kRoundBegin, r, s);
             int rc = launch_round_t<KB, VB, true>(g, a, s, dyn);
             if (rc) return rc;

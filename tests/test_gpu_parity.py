@@ -468,6 +468,39 @@ def test_constant_digits_match_oracle(case, shared):
         assert np.array_equal(from_dev(dv, vb).astype(np.uint64), ev)
 
 
+# ------------------------------------------------ look-back over all tiles of a round
+
+# One-call sorts whose look-back words fit one per (tile, digit), at the last such size
+# and past it, and those of a ring whose slots are used again (over 1024 tiles of 8192 or
+# 16384 slots at 8-bit digits; few digits make many slots).
+CHAIN = [
+    ("uniform", (1 << 24) + 16385, 8, 0, 8, 1024),
+    ("few", (1 << 24) + (1 << 22), 8, 4, 8, 4096),
+    ("zipf", (1 << 25) + 77, 4, 4, 8, 1024),
+    ("zipf", (1 << 25) + (1 << 24) - 1, 4, 0, 8, 32768),
+    ("uniform", (1 << 25) + 5, 8, 8, 7, 2048),
+    ("low20", (1 << 25) + 8191, 4, 8, 3, 1024),
+]
+
+
+@pytest.mark.parametrize("case", CHAIN, ids=lambda c: "-".join(map(str, c)))
+def test_long_lookback_matches_stable_sort(case):
+    """The order of a stable sort, exactly: payloads are positions."""
+    dist, n, kb, vb, bits, b = case
+    say(f"long look-back {case}")
+    keys, _ = inputs(dist, n, kb, vb, seed=13)
+    dk = to_dev(keys)
+    dv = torch.arange(n, device="cuda").to(torch.int32 if vb == 4 else torch.int64) if vb else None
+    want = dk.to(torch.int64)
+    want = want & 0xFFFFFFFF if kb == 4 else want ^ -(1 << 63)
+    order = torch.sort(want, stable=True)[1]
+    ek = dk[order]
+    radsort.sort_(dk, dv, digit_bits=bits, block_elems=b, check=True)
+    assert torch.equal(dk, ek)
+    if vb:
+        assert torch.equal(dv.to(torch.int64), order)
+
+
 # ---------------------------------------------------------------- arrays sorted on chip
 
 SMALL_N = [2, 63, 256, 511, 512, 513, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8191, 8192, 8193]
