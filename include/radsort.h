@@ -210,10 +210,12 @@ uint64_t radsort_oop_workspace_bytes(uint64_t n, int key_bytes, int payload_byte
  * is elements [offsets[i], offsets[i+1]) of the key plane (and of the payload
  * plane).  Arrays of at most 8192 elements (4096 for records of 12 or more bytes)
  * are each sorted whole in LDS by one workgroup, with 8-bit digits and no
- * workspace.  Arrays of up to 4 423 680 elements are sorted by Radsort (Alg. 2:
- * setup, n_t x sortPhase + fixupPhase, finalize) run by one workgroup per array,
- * all of them in one launch, with 5-bit digits and b = 1024 (each of at most 256
- * workgroups owns a T of 2 * 32 * 1024 elements in the workspace).  Larger arrays
+ * workspace.  Arrays of up to 4 423 680 elements share a scratch of 2 * 32 * 1024
+ * elements for each of at most 256 workgroups in the workspace: those that fit it
+ * are sorted out of place there (Alg. 1, 8-bit digits), many at a time; the
+ * others by Radsort (Alg. 2: setup, n_t x sortPhase + fixupPhase, finalize) run by one
+ * workgroup per array, all of them in one launch, with 5-bit digits and b = 1024,
+ * each workgroup with its part of the scratch as its T.  Larger arrays
  * each run the Radsort steps with the block size and digit width of their size
  * class in `tuning` (NULL: b = 2^ceil(log2 sqrt n) in [64, 2048] and 8-bit digits,
  * after the b in Theta(sqrt n) of Sec. 3), in launch forms that need no

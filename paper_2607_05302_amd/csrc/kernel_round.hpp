@@ -1,5 +1,8 @@
 // One digit round of Radsort's sortPhase (Alg. 5) on the GPU, and the
-// out-of-place round of Alg. 1 built from the same tile code.
+// out-of-place round of Alg. 1 built from the same tile code.  The default draw order
+// with digits of at most 8 bits and blocks of 1024 elements or more runs kernel_tile.hpp
+// instead, with the same protocol; this kernel takes the rest, and the out-of-place
+// round where the tables of kernel_seg.hpp do not fit the workspace.
 //
 // A tile is E consecutive element slots of the logical block sequence
 // sigma .. f-1 (slot s of logical block L holds element s if s < len(L)).  How

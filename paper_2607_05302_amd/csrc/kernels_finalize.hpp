@@ -246,13 +246,145 @@ __global__ void k_fin_order(const uint32_t* __restrict__ nxt, const uint32_t* __
     }
 }
 
+// ---- finalize of a packed state ------------------------------------------------------
+//
+// After the packed round, block q of bucket d holds the ranks whose final positions
+// lie in block g = floor(est[d] / b) + q of A, each at the slot it has there: slots
+// lo .. hi - 1 with lo = est[d] mod b for q = 0, else 0.  So the data needs no gap
+// closed, only blocks moved: every block g < floor(n/b) of A is the home of its
+// "primary", the block whose slots reach the end of g (exactly one per g).  Each
+// other block with data is the last block of its bucket, ending inside a block of
+// A or lying in the partial tail [floor(n/b) b, n); it moves to a spare block (of
+// T or X) and is copied into place afterwards (k_pack_merge), its slots only, over
+// the garbage the primary brought into those slots.  Blocks without data (the
+// head start, the unallocated ones, a bucket's empty head or empty last block)
+// take the spare blocks left.  Spare k is physical k for k < 2 sigma, else
+// npi_eq + k - 2 sigma.
+
+__device__ __forceinline__ uint32_t pack_spare(uint32_t k, uint32_t sigma, uint32_t npi_eq)
+{
+    return k < 2 * sigma ? k : npi_eq + (k - 2 * sigma);
+}
+
+// What bucket d has: a spare block (its last block, with data, that is no primary) and
+// an empty block.
+__device__ __forceinline__ void pack_bucket(const uint32_t* est, uint32_t d, uint64_t n,
+                                            uint32_t sigma, uint32_t log2b, bool& spare,
+                                            bool& empty)
+{
+    const uint32_t b = 1u << log2b;
+    const uint64_t nA = n >> log2b;
+    const uint64_t e0 = est[d], e1 = d + 1 < sigma ? est[d + 1] : n;
+    const uint64_t c = e1 > e0 ? e1 - e0 : 0, o = e0 & (b - 1);
+    spare = false;
+    if (c) {
+        const uint64_t ql = (o + c - 1) >> log2b, gl = (e0 >> log2b) + ql;
+        const uint64_t hl = o + c - (ql << log2b);
+        spare = gl >= nA || hl < b;
+    }
+    empty = c == 0 || ((o + c) & (b - 1)) == 0;
+}
+
+// The bucket table (one workgroup): tab[d] = rank of bucket d's spare block among
+// those of buckets before it (~0: none), tab[sigma + d] = rank of its empty block
+// (~0: none), tab[2 sigma] and tab[2 sigma + 1] the totals.  sh: 2 sigma words of LDS.
+template <int NT>
+__device__ __forceinline__ void pack_table(const uint32_t* est, uint64_t n, uint32_t sigma,
+                                           uint32_t log2b, uint32_t* sh, uint32_t* tmp,
+                                           uint32_t* tab)
+{
+    for (uint32_t d = threadIdx.x; d < sigma; d += NT) {
+        bool spare, empty;
+        pack_bucket(est, d, n, sigma, log2b, spare, empty);
+        sh[d] = spare;
+        sh[sigma + d] = empty;
+    }
+    __syncthreads();
+    const uint32_t ns = block_excl_scan<NT>(sh, sigma, tmp);
+    const uint32_t ne = block_excl_scan<NT>(sh + sigma, sigma, tmp);
+    for (uint32_t d = threadIdx.x; d < sigma; d += NT) {
+        bool spare, empty;
+        pack_bucket(est, d, n, sigma, log2b, spare, empty);
+        tab[d] = spare ? sh[d] : ~0u;
+        tab[sigma + d] = empty ? sh[sigma + d] : ~0u;
+    }
+    if (threadIdx.x == 0) {
+        tab[2 * sigma] = ns;
+        tab[2 * sigma + 1] = ne;
+    }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_pack_table(const uint32_t* __restrict__ est, uint64_t n,
+                                                   uint32_t sigma, uint32_t log2b,
+                                                   uint32_t* __restrict__ tab)
+{
+    extern __shared__ uint32_t sh[];  // 2 sigma words
+    __shared__ uint32_t tmp[NT / 64 + 1];
+    pack_table<NT>(est, n, sigma, log2b, sh, tmp, tab);
+}
+
+// The home of logical block L < npi (npi = npi_eq + sigma): its primary's A block, a
+// spare block, or (top bit set) a spare block for a block without data.  f <= npi.
+__device__ __forceinline__ uint32_t pack_home(uint32_t L, const uint32_t* S, const uint32_t* est,
+                                              uint32_t f, const uint32_t* tab, uint64_t n,
+                                              uint32_t sigma, uint32_t log2b, uint32_t npi_eq,
+                                              uint32_t* err)
+{
+    const uint32_t b = 1u << log2b;
+    const uint64_t nA = n >> log2b;
+    const uint32_t ns = tab[2 * sigma], ne = tab[2 * sigma + 1];
+    if (L < sigma) return pack_spare(ns + L, sigma, npi_eq) | kGarbage;
+    if (L >= f) return pack_spare(ns + sigma + ne + (L - f), sigma, npi_eq) | kGarbage;
+    uint32_t lo_d = 0, hi_d = sigma;  // the last bucket d with S[d] <= L
+    while (hi_d - lo_d > 1) {
+        const uint32_t mid = (lo_d + hi_d) >> 1;
+        if (S[mid] <= L) lo_d = mid;
+        else hi_d = mid;
+    }
+    const uint32_t d = lo_d, q = L - S[d];
+    const uint64_t e0 = est[d], e1 = d + 1 < sigma ? est[d + 1] : n;
+    const uint64_t c = e1 > e0 ? e1 - e0 : 0, o = e0 & (b - 1);
+    const uint64_t start = (uint64_t)q << log2b, g = (e0 >> log2b) + q;
+    const uint64_t lo = q == 0 ? o : 0;
+    const uint64_t hi = o + c > start ? min<uint64_t>(b, o + c - start) : 0;
+    if (hi > lo && g < nA && hi == b) return 2 * sigma + (uint32_t)g;
+    const uint32_t r = hi <= lo ? tab[sigma + d] : tab[d];
+    if (r == ~0u) raise_error(err, kErrBounds);  // never for a consistent plan
+    const uint32_t rk = r == ~0u ? 0 : r;
+    return hi <= lo ? pack_spare(ns + sigma + rk, sigma, npi_eq) | kGarbage
+                    : pack_spare(rk, sigma, npi_eq);
+}
+
+__global__ void k_pack_homes(const uint32_t* __restrict__ S, const uint32_t* __restrict__ est,
+                             const uint32_t* __restrict__ f_ptr, const uint32_t* __restrict__ tab,
+                             uint64_t n, uint32_t sigma, uint32_t log2b, uint32_t npi_eq,
+                             uint32_t npi, uint32_t* __restrict__ homes,
+                             uint32_t* __restrict__ err)
+{
+    const uint32_t f = min(*f_ptr, npi);
+    for (uint32_t L = blockIdx.x * blockDim.x + threadIdx.x; L < npi;
+         L += gridDim.x * blockDim.x)
+        homes[L] = pack_home(L, S, est, f, tab, n, sigma, log2b, npi_eq, err);
+}
+
 // The whole preparation of F1 (next, the doubling steps, ranks, cycle lengths,
 // the scan of the leaders' cycle lengths and the order array) plus the gap
 // prefix of F2 and the clearing of F2's chunk flags, in one workgroup with the
 // doubling state in LDS, for n_pi <= kFinSmallNodes.  Same results as
 // k_fin_init .. k_fin_order and k_fin_gaps: rank, clen, ord and *M_out (the
 // number of nodes to move) in global memory for k_fin_save / k_fin_move, and
-// gap[0 .. sigma] for F2 / F3.
+// gap[0 .. sigma] for F2 / F3.  A packed state (pk.pack given) has no F2; its bucket table
+// and its blocks' homes are made here too, from S and est in LDS: as two launches before
+// this one (k_pack_table, k_pack_homes) they made a sort of 2^20 uint32 pairs 201 us instead
+// of 197, one of 3 M uint64 + uint32 records 459 instead of 454.  n_pi >= 3 sigma there, so the tables fit the arrays of the doubling
+// state.
+struct PackPtrs {
+    uint32_t* pack;       // null: not a packed state
+    const uint32_t *S, *est;
+    uint64_t n;
+    uint32_t npi_eq;
+};
 constexpr uint32_t kFinSmallNodes = 8192;
 template <int NT>
 __global__ __launch_bounds__(NT) void k_fin_prep_small(
@@ -260,8 +392,7 @@ __global__ __launch_bounds__(NT) void k_fin_prep_small(
     const uint32_t* __restrict__ Pidx, const uint32_t* __restrict__ Plen, uint32_t sigma,
     uint32_t log2b, uint32_t npi, uint32_t* __restrict__ rank, uint32_t* __restrict__ clen,
     uint32_t* __restrict__ ord, uint32_t* __restrict__ M_out, uint32_t* __restrict__ gap,
-    uint32_t* __restrict__ flags, uint64_t nflags, uint32_t* __restrict__ err,
-    const uint32_t* __restrict__ homes)
+    uint32_t* __restrict__ flags, uint64_t nflags, uint32_t* __restrict__ err, PackPtrs pk)
 {
     constexpr uint32_t PER = kFinSmallNodes / NT;  // nodes per thread
     __shared__ uint32_t nx[kFinSmallNodes], J[kFinSmallNodes], Vs[kFinSmallNodes],
@@ -272,9 +403,38 @@ __global__ __launch_bounds__(NT) void k_fin_prep_small(
         if (tid == 0) raise_error(err, kErrBounds);
         return;
     }
-    for (uint64_t i = tid; i < nflags; i += NT) flags[i] = 0;
+    const bool packed = pk.pack != nullptr;
+    uint32_t home[PER];
+    if (packed) {
+        if (3 * sigma > npi || 2 * sigma + 2 > kFinSmallNodes) {  // never
+            if (tid == 0) raise_error(err, kErrBounds);
+            return;
+        }
+        uint32_t *const Ss = nx, *const est_s = nx + sigma, *const tab = Os;
+        for (uint32_t d = tid; d < sigma; d += NT) {
+            Ss[d] = pk.S[d];
+            est_s[d] = pk.est[d];
+        }
+        __syncthreads();
+        pack_table<NT>(est_s, pk.n, sigma, log2b, J, tmp, tab);
+        __syncthreads();
+        for (uint32_t i = tid; i < 2 * sigma + 2; i += NT) pk.pack[i] = tab[i];
+#pragma unroll
+        for (uint32_t k = 0; k < PER; k++) {
+            const uint32_t L = tid + k * NT;
+            home[k] = L < npi ? pack_home(L, Ss, est_s, min(f, npi), tab, pk.n, sigma, log2b,
+                                          pk.npi_eq, err)
+                              : 0u;
+        }
+        __syncthreads();  // the tables were read
+    } else {
+        for (uint64_t i = tid; i < nflags; i += NT) flags[i] = 0;
+    }
     // next(pi[L]) = rot(L), garbage bit for unallocated L; J = next, (V, O) = (p, 0)
-    for (uint32_t L = tid; L < npi; L += NT) {
+#pragma unroll
+    for (uint32_t k = 0; k < PER; k++) {
+        const uint32_t L = tid + k * NT;
+        if (L >= npi) break;
         uint32_t p = pi[L];
         if (p >= npi) {  // never for a permutation
             raise_error(err, kErrBounds);
@@ -282,9 +442,9 @@ __global__ __launch_bounds__(NT) void k_fin_prep_small(
         }
         uint32_t to = L + sigma < npi ? L + sigma : L + sigma - npi;
         uint32_t gb = (L < sigma || L >= f) ? kGarbage : 0u;
-        if (homes) {  // packed state
-            to = homes[L] & ~kGarbage;
-            gb = homes[L] & kGarbage;
+        if (packed) {
+            to = home[k] & ~kGarbage;
+            gb = home[k] & kGarbage;
             if (to >= npi) to = p;  // never for a consistent table
         }
         nx[p] = to | gb;
@@ -361,6 +521,7 @@ __global__ __launch_bounds__(NT) void k_fin_prep_small(
         }
     }
     if (tid == 0) *M_out = M;
+    if (packed) return;
     // F2's gap prefix: unused room of the partial blocks of P before each entry
     __syncthreads();  // Os is free
     const uint32_t b = 1u << log2b;
@@ -761,118 +922,7 @@ __global__ __launch_bounds__(kFinLdsThreads) void k_fin_move_lds(
     }
 }
 
-// ---- finalize of a packed state ------------------------------------------------------
-//
-// After the packed round, block q of bucket d holds the ranks whose final positions
-// lie in block g = floor(est[d] / b) + q of A, each at the slot it has there: slots
-// lo .. hi - 1 with lo = est[d] mod b for q = 0, else 0.  So the data needs no gap
-// closed, only blocks moved: every block g < floor(n/b) of A is the home of its
-// "primary", the block whose slots reach the end of g (exactly one per g).  Each
-// other block with data is the last block of its bucket, ending inside a block of
-// A or lying in the partial tail [floor(n/b) b, n); it moves to a spare block (of
-// T or X) and is copied into place afterwards (k_pack_merge), its slots only, over
-// the garbage the primary brought into those slots.  Blocks without data (the
-// head start, the unallocated ones, a bucket's empty head or empty last block)
-// take the spare blocks left.  Spare k is physical k for k < 2 sigma, else
-// npi_eq + k - 2 sigma.
-
-__device__ __forceinline__ uint32_t pack_spare(uint32_t k, uint32_t sigma, uint32_t npi_eq)
-{
-    return k < 2 * sigma ? k : npi_eq + (k - 2 * sigma);
-}
-
-// The bucket table (one workgroup): tab[d] = rank of bucket d's spare block among
-// those of buckets before it (~0: none), tab[sigma + d] = rank of its empty block
-// (~0: none), tab[2 sigma] and tab[2 sigma + 1] the totals.
-template <int NT>
-__global__ __launch_bounds__(NT) void k_pack_table(const uint32_t* __restrict__ est, uint64_t n,
-                                                   uint32_t sigma, uint32_t log2b,
-                                                   uint32_t* __restrict__ tab)
-{
-    extern __shared__ uint32_t sh[];  // 2 sigma words
-    __shared__ uint32_t tmp[NT / 64 + 1];
-    const uint32_t b = 1u << log2b;
-    const uint64_t nA = n >> log2b;
-    for (uint32_t d = threadIdx.x; d < sigma; d += NT) {
-        const uint64_t e0 = est[d], e1 = d + 1 < sigma ? est[d + 1] : n;
-        const uint64_t c = e1 > e0 ? e1 - e0 : 0, o = e0 & (b - 1);
-        bool spare = false;
-        if (c) {
-            const uint64_t ql = (o + c - 1) >> log2b, gl = (e0 >> log2b) + ql;
-            const uint64_t hl = o + c - (ql << log2b);
-            spare = gl >= nA || hl < b;
-        }
-        sh[d] = spare;
-        sh[sigma + d] = c == 0 || ((o + c) & (b - 1)) == 0;
-    }
-    __syncthreads();
-    const uint32_t ns = block_excl_scan<NT>(sh, sigma, tmp);
-    const uint32_t ne = block_excl_scan<NT>(sh + sigma, sigma, tmp);
-    for (uint32_t d = threadIdx.x; d < sigma; d += NT) {
-        const uint64_t e0 = est[d], e1 = d + 1 < sigma ? est[d + 1] : n;
-        const uint64_t c = e1 > e0 ? e1 - e0 : 0, o = e0 & (b - 1);
-        bool spare = false;
-        if (c) {
-            const uint64_t ql = (o + c - 1) >> log2b, gl = (e0 >> log2b) + ql;
-            const uint64_t hl = o + c - (ql << log2b);
-            spare = gl >= nA || hl < b;
-        }
-        const bool empty = c == 0 || ((o + c) & (b - 1)) == 0;
-        tab[d] = spare ? sh[d] : ~0u;
-        tab[sigma + d] = empty ? sh[sigma + d] : ~0u;
-    }
-    if (threadIdx.x == 0) {
-        tab[2 * sigma] = ns;
-        tab[2 * sigma + 1] = ne;
-    }
-}
-
-// homes[L] for every logical block L < npi (npi = npi_eq + sigma): its primary's A
-// block, a spare block, or (top bit set) a spare block for a block without data.
-__global__ void k_pack_homes(const uint32_t* __restrict__ S, const uint32_t* __restrict__ est,
-                             const uint32_t* __restrict__ f_ptr, const uint32_t* __restrict__ tab,
-                             uint64_t n, uint32_t sigma, uint32_t log2b, uint32_t npi_eq,
-                             uint32_t npi, uint32_t* __restrict__ homes,
-                             uint32_t* __restrict__ err)
-{
-    const uint32_t b = 1u << log2b, f = min(*f_ptr, npi);
-    const uint64_t nA = n >> log2b;
-    const uint32_t ns = tab[2 * sigma], ne = tab[2 * sigma + 1];
-    for (uint32_t L = blockIdx.x * blockDim.x + threadIdx.x; L < npi;
-         L += gridDim.x * blockDim.x) {
-        uint32_t h;
-        if (L < sigma) {
-            h = pack_spare(ns + L, sigma, npi_eq) | kGarbage;
-        } else if (L >= f) {
-            h = pack_spare(ns + sigma + ne + (L - f), sigma, npi_eq) | kGarbage;
-        } else {
-            uint32_t lo_d = 0, hi_d = sigma;  // the last bucket d with S[d] <= L
-            while (hi_d - lo_d > 1) {
-                const uint32_t mid = (lo_d + hi_d) >> 1;
-                if (S[mid] <= L) lo_d = mid;
-                else hi_d = mid;
-            }
-            const uint32_t d = lo_d, q = L - S[d];
-            const uint64_t e0 = est[d], e1 = d + 1 < sigma ? est[d + 1] : n;
-            const uint64_t c = e1 > e0 ? e1 - e0 : 0, o = e0 & (b - 1);
-            const uint64_t start = (uint64_t)q << log2b, g = (e0 >> log2b) + q;
-            const uint64_t lo = q == 0 ? o : 0;
-            const uint64_t hi = o + c > start ? min<uint64_t>(b, o + c - start) : 0;
-            if (hi <= lo) {
-                const uint32_t r = tab[sigma + d];
-                h = pack_spare(ns + sigma + (r == ~0u ? 0 : r), sigma, npi_eq) | kGarbage;
-                if (r == ~0u) raise_error(err, kErrBounds);  // never for a consistent plan
-            } else if (g < nA && hi == b) {
-                h = 2 * sigma + (uint32_t)g;
-            } else {
-                const uint32_t r = tab[d];
-                h = pack_spare(r == ~0u ? 0 : r, sigma, npi_eq);
-                if (r == ~0u) raise_error(err, kErrBounds);  // never for a consistent plan
-            }
-        }
-        homes[L] = h;
-    }
-}
+// ---- finalize of a packed state: after F1 ---------------------------------------------
 
 // After F1: workgroup d copies the slots of bucket d's spare block (if it has one)
 // from that block into A.
@@ -1078,21 +1128,22 @@ int finalize_parallel(FinArgs<KB, VB>& a, uint32_t compact_grid, uint32_t lds_gr
     const uint32_t* M_ptr;  // total number of nodes to move
     uint32_t* gap;          // F2's gap prefix
     // a packed state: its bucket table, then every logical block's home (in o1,
-    // which the preparation below reads before it writes o1)
+    // which the preparation below reads before it writes o1); a small one's are made there
     const uint32_t* homes = nullptr;
-    if (a.pack) {
+    const bool small = npi <= kFinSmallNodes;
+    if (a.pack && !small) {
         hipLaunchKernelGGL(k_pack_table<256>, dim3(1), dim3(256), 8 * a.sigma, s, a.est, a.n,
                            a.sigma, a.log2b, a.pack);
         hipLaunchKernelGGL(k_pack_homes, dim3(grid), dim3(256), 0, s, a.S, a.est, a.f, a.pack,
                            a.n, a.sigma, a.log2b, a.npi_eq, npi, f.o1, a.err);
         homes = f.o1;
     }
-    const bool small = npi <= kFinSmallNodes;
     if (small) {
         // F1's preparation, F2's gaps and flags in one workgroup
         hipLaunchKernelGGL(k_fin_prep_small<1024>, dim3(1), dim3(1024), 0, s, a.pi, a.f, a.Pidx,
                            a.Plen, a.sigma, a.log2b, npi, rank, clen, f.ord, f.sums, f.o0,
-                           f.flags, f.nflags, a.err, homes);
+                           f.flags, f.nflags, a.err,
+                           PackPtrs{a.pack, a.S, a.est, a.n, a.npi_eq});
         M_ptr = f.sums;
         gap = f.o0;
     } else {

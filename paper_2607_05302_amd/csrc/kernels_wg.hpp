@@ -1,4 +1,5 @@
-// Many mid-size arrays in one launch: each workgroup takes one array at a time
+// The arrays of a batch that are too large to be sorted out of place in the batch's
+// workspace (kernel_seg.hpp) and small enough for one workgroup, in one launch: each workgroup takes one array at a time
 // (claimed from a counter) and runs the whole of Radsort on it by itself, the
 // sequential algorithm of Sec. 2 with the work of each step spread over the
 // workgroup's threads: setup (Alg. 4), n_t rounds of sortPhase (Alg. 5) and
@@ -10,8 +11,8 @@
 // 13 for 64-bit) and blocks of b = 2^kWgLog2b = 1024 elements, so that pi, pi'
 // (n_pi <= kWgMaxBlocks 16-bit entries each) live in LDS and T (2 sigma b =
 // 65536 elements per plane) is small; each workgroup owns one such T (its slot
-// of the workspace).  On a batch of 4096 arrays of up to 2^22 uint32 pairs this
-// took 137.4 ms, against 145.9 ms with 4-bit digits (b = 1024), 139.8 ms with
+// of the workspace).  On a batch of 4096 arrays of up to 2^22 uint32 pairs, all of
+// them sorted by this kernel (before kernel_seg.hpp), it took 137.4 ms, against 145.9 ms with 4-bit digits (b = 1024), 139.8 ms with
 // 6-bit digits (b = 1024, twice the workspace) and 174.6 ms with 6-bit digits
 // and b = 512 (twice the blocks: finalize and the block tables cost more).
 //

@@ -95,10 +95,11 @@ template <int KB, int VB, bool WIDE, bool OOP = false> struct TileCfg {
     static constexpr int E = 64 * WAVES * ITEMS;
 };
 
-// The Radsort round's tile for large arrays of records of at most 8 bytes: shape 1
+// k_round's tile for large arrays of records of at most 8 bytes: shape 1
 // with twice the slots per lane (4-byte keys: 16384-slot tiles; 8-byte keys without
 // payload: 8192), one workgroup per compute unit.  Its digit runs per tile are twice
-// as long and the super-tiles half as many.  Measured with 8-bit digits: uint32 +
+// as long and the super-tiles half as many.  Measured with 8-bit digits (b >= 1024 and
+// the default draw order now run k_tile_round instead): uint32 +
 // uint32 at 2^28, b = 2048, 8.20-8.27 ms per sort against 8.47 ms with the smaller
 // tile (from 2^25 to 2^27 elements no faster: fewer tiles in flight, so it is taken
 // from kLargeTileMin on); uint64 keys at b = 4096, 18.8 against 19.6 ms at 2^28 and
