@@ -149,7 +149,8 @@ constexpr uint32_t kModeRun = 0, kModeSkip = 1, kModePacked = 2;
 // the n mod b tail of A copied to physical block sigma, the other pi buffer
 // cleared to "unset", f = sigma + floor(n/b) + 1 and P = the tail block, then
 // dummies (Pidx, Plen, f_out: index 0 of the per-round arrays); the first
-// round's look-back ring (ring_words words) cleared.  Both pi buffers hold npx entries,
+// round's look-back ring (ring_words words) and the call's counters (count_words words,
+// in one-call sorts with the digit counts before them) cleared.  Both pi buffers hold npx entries,
 // those from npi on (a packed round's extra blocks) unset.
 template <int KB, int VB>
 __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
@@ -160,11 +161,15 @@ __global__ void k_setup(typename UInt<KB>::T* __restrict__ Ak,
                         uint32_t* __restrict__ pi_next, uint32_t* __restrict__ blen,
                         uint64_t* __restrict__ opened, uint32_t* __restrict__ Pidx,
                         uint32_t* __restrict__ Plen, uint32_t* __restrict__ f_out,
-                        uint32_t* __restrict__ ring, uint64_t ring_words)
+                        uint32_t* __restrict__ ring, uint64_t ring_words,
+                        uint32_t* __restrict__ counts, uint32_t count_words)
 {
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < ring_words;
          i += (uint64_t)gridDim.x * blockDim.x)
         ring[i] = 0;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < count_words;
+         i += gridDim.x * blockDim.x)
+        counts[i] = 0;
     const uint64_t nb = n >> log2b, tail = n - (nb << log2b);
     const uint32_t f = sigma + (uint32_t)nb + 1;
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < npx || i < tail;

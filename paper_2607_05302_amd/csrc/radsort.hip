@@ -275,7 +275,9 @@ int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bit
     // workgroups) where its rows fit the memory laid out for the ring and the larger
     // super-tiles' rows; else super-tiles of at least 2^kSuperSlotsLog2 slots.  At
     // 2^20 uint32 pairs super-tiles of 2^16 slots were 17 workgroups: 20 us per pass.
-    g.st_log2 = digit_start_bytes(g, g.tiles) + csum_bytes(g, g.tiles) <=
+    // Look-back words in the rows' place hold counts of up to kRowValue.
+    g.st_log2 = n <= kRowValue &&
+                        digit_start_bytes(g, g.tiles) + csum_bytes(g, g.tiles) <=
                         count_word_bytes(g) + csum_bytes(g, g.lay_supers) +
                             digit_start_bytes(g, g.lay_supers)
                     ? 0u
@@ -486,7 +488,7 @@ struct radsort_state {
     // a look-back word per (tile, digit) in the place of the ring and the digit starts
     // where they fit (st_log2), else a ring of them in the place of the ring; they are
     // zeroed per round
-    bool chain_rows() const { return modes() && g.st_log2 == 0 && g.n <= kRowValue; }
+    bool chain_rows() const { return modes() && g.st_log2 == 0; }
     uint64_t zero_from() const { return chain_rows() ? L.stcnt : L.zero; }
     uint64_t zero_words() const { return (L.zero + L.zero_bytes - zero_from()) / 4; }
     // entries of pi: a packed round's extra blocks too
@@ -683,7 +685,6 @@ template <int KB, int VB> struct Ops {
         g_timer.mark(kStart, 0, s);
         // every round is planned later from its own digit counts
         const uint64_t from = st->modes() ? st->L.est : st->L.ctr;  // est, then the counters
-        launch_fill(st->u32(from), (st->L.ctr - from) / 4 + g.nt + 8, 0, s);
         uint64_t work = std::max<uint64_t>(st->npx(), g.n & (g.b - 1));
         uint32_t grid = (uint32_t)std::min<uint64_t>((work + 255) / 256, 4096);
         hipLaunchKernelGGL((k_setup<KB, VB>), dim3(grid), dim3(256), 0, s, (K*)st->keys,
@@ -691,7 +692,8 @@ template <int KB, int VB> struct Ops {
                            g.log2b, g.sigma, g.npi, st->npx(), st->pi(0), st->pi(1), st->u32(st->L.blen),
                            (uint64_t*)(st->ws + st->L.opened), st->u32(st->L.Pidx),
                            st->u32(st->L.Plen), st->u32(st->L.f), st->u32(st->zero_from()),
-                           st->zero_words());
+                           st->zero_words(), st->u32(from),
+                           (uint32_t)((st->L.ctr - from) / 4 + g.nt + 8));
         if (st->modes()) {
             // 16384 keys to a workgroup, more where that makes over 2048 workgroups
             const uint64_t per = align_up(std::max<uint64_t>(16384, (g.n + 2047) / 2048), 8192);

@@ -114,3 +114,15 @@ def test_max_segments_past_2e32():
     assert bool(seen.all()), "the indices are not a permutation of each array"
     del keys, vals, orig, seen
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("bits", [1, 2])
+def test_few_digits_past_2_30(bits):
+    """Digits of few values leave the tables of a round small, so that arrays of over
+    2^30 keys come near the forms for small arrays, whose look-back words hold 30 bits."""
+    n = (1 << 30) + 16385
+    print(f"few digits: n = {n} uint32 keys, {bits}-bit digits", flush=True)
+    keys = workloads.uniform_t(workloads.SEED_LARGE, n, 4, DEV, start=0).to(torch.int32)
+    want = torch.sort(keys ^ (-(1 << 31)))[0] ^ (-(1 << 31))
+    radsort.sort_(keys, digit_bits=bits, block_elems=2048, check=True)
+    assert torch.equal(keys, want)
