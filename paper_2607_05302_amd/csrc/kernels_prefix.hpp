@@ -101,7 +101,7 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
     constexpr int U = 16;  // loads in flight per thread
     __shared__ uint32_t h[kHistWords];
     __shared__ uint32_t bphys[OOP ? 1 : kMaxSuperBlocks], blen_s[OOP ? 1 : kMaxSuperBlocks];
-    __shared__ uint32_t last;
+    __shared__ uint32_t last, tmp[NT / 64];
     const uint32_t sigma = 1u << bits, dmask = sigma - 1, two_sigma = 2 * sigma;
     const uint32_t clog = min(kCopiesLog2, kHistLog2 - bits), copies = 1u << clog;
     const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -210,9 +210,9 @@ __global__ __launch_bounds__(NT) void k_supertile_counts(
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();  // the totals row is written by this workgroup; h is free
     const bool packed = plan == 3;
-    plan_round<NT>(cnt + (uint64_t)(gridDim.x - 1) * sigma, sigma, log2b, h, h + sigma,
-                   h + 2 * sigma, pp.S, pp.Pidx, pp.Plen, pp.f,
-                   packed || plan == 2 ? pp.est : nullptr, packed);
+    static_assert(kHistWords >= 2 << 11, "h holds two arrays of sigma words, sigma up to 2^11");
+    plan_round<NT>(cnt + (uint64_t)(gridDim.x - 1) * sigma, sigma, log2b, h, h + sigma, tmp, pp.S,
+                   pp.Pidx, pp.Plen, pp.f, packed || plan == 2 ? pp.est : nullptr, packed);
 }
 
 // The plans of all rounds of a one-call sort at once: the digit counts of every key

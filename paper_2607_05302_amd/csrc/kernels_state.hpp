@@ -101,7 +101,7 @@ struct PlanPtrs {
 };
 
 // One round of the plan from the digit counts cnt[0..sigma) of its input.  C and
-// E are sigma words of LDS each, tmp NT/64 + 1; est may be null (Radsort itself
+// E are sigma words of LDS each, tmp NT/64; est may be null (Radsort itself
 // needs no element starts).  Contains barriers: every thread must call it.
 //
 // packed (a Radsort round that is the last before finalize; est given): bucket d
