@@ -30,7 +30,7 @@ struct SegArr {
     uint32_t n;       // elements
     uint32_t scr64;   // first record in the scratch planes, in units of 64
     uint32_t tile0;   // the array's first tile
-    uint32_t pad;
+    uint32_t group;
 };
 
 // Look-back word of (tile, digit): the tile's count, or the count of its array up to and
@@ -51,9 +51,10 @@ template <int KB, int VB> struct SegArgs {
     const SegArr* arr;     // all arrays of the path
     const uint32_t* map;   // tile -> array
     uint32_t a0, t0;       // first array and first tile of the group
+    uint32_t na, group;    // its arrays, its number
     uint32_t* hist;        // [array of the group][n_t][256]: counts, then element starts
     uint32_t* arrived;     // [array of the group]: tiles counted
-    uint32_t* rounds;      // [array of the group]: bit r: round r runs
+    uint32_t* rounds;      // [array of the group]: bit r: round r runs; 0 until counted
     uint32_t* state;       // [tile of the group][256]: look-back words
     uint32_t* ctr;         // [n_t]: tiles claimed
     uint32_t* err;
@@ -62,11 +63,14 @@ template <int KB, int VB> struct SegArgs {
 
 // The arrays of lo < n <= hi elements in order, with their scratch places and tiles: the
 // running sum of their sizes in units of 64 records is cut into groups of G64.  One workgroup.
+// The host laid the tables out and chose the launches by its copy of the offsets.  Where the
+// device's give another number of arrays or tiles, every entry is marked unused, and the
+// counting pass reports the first tile it looks at.
 template <int NT>
 __global__ __launch_bounds__(NT) void k_seg_plan(const uint64_t* __restrict__ offsets,
                                                  uint32_t nseg, uint64_t lo, uint64_t hi,
-                                                 uint32_t G64, uint32_t E,
-                                                 SegArr* __restrict__ arr, uint32_t count)
+                                                 uint32_t G64, uint32_t E, SegArr* arr,
+                                                 uint32_t count, uint32_t* map, uint32_t tiles)
 {
     __shared__ uint32_t a[NT], b[NT], c[NT], tmp[NT / 64 + 1];
     uint32_t idx = 0, pos = 0, tile = 0;
@@ -87,12 +91,17 @@ __global__ __launch_bounds__(NT) void k_seg_plan(const uint64_t* __restrict__ of
         const uint32_t nb = block_excl_scan<NT>(b, NT, tmp);
         const uint32_t nc = block_excl_scan<NT>(c, NT, tmp);
         const uint32_t at = idx + a[threadIdx.x], p = pos + b[threadIdx.x];
-        if (n && at < count) arr[at] = SegArr{o0, (uint32_t)n, p % G64, tile + c[threadIdx.x], 0};
+        if (n && at < count)
+            arr[at] = SegArr{o0, (uint32_t)n, p % G64, tile + c[threadIdx.x], p / G64};
         idx += na;
         pos += nb;
         tile += nc;
         __syncthreads();
     }
+    if (idx == count && tile == tiles) return;
+    wg_global_handoff();  // the entries above land before the marks
+    for (uint32_t i = threadIdx.x; i < count; i += NT) arr[i] = SegArr{0, 0, 0, 0, 0};
+    for (uint32_t t = threadIdx.x; t < tiles; t += NT) map[t] = ~0u;
 }
 
 // map[tile] = array
@@ -130,9 +139,14 @@ __global__ __launch_bounds__(NT) void k_seg_hist(SegArgs<KB, 0> a, uint32_t E)
     __shared__ uint32_t last, mask;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t tile = a.t0 + blockIdx.x, ai = a.map[tile];
-    const SegArr e = a.arr[ai];
+    // Only where the host's and the device's offsets disagree: the tile's array is not one of
+    // the group's, or was placed in another group's scratch.  Such an array is never counted
+    // in full, so no round of it runs.
+    const bool ours = ai - a.a0 < a.na;
+    SegArr e{};
+    if (ours) e = a.arr[ai];
     const uint32_t ti = tile - e.tile0, ntiles = (e.n + E - 1) / E;
-    if (ti >= ntiles) {  // never when the host and device offsets agree
+    if (!ours || ti >= ntiles || e.group != a.group) {
         if (tid == 0) raise_error(a.err, kErrBounds);
         return;
     }
@@ -221,15 +235,13 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_seg_round(SegArgs<KB, VB> a
     __syncthreads();
     const uint32_t lt = claimed, tile = a.t0 + lt;  // claimed < grid = tiles of the group
     const uint32_t ai = a.map[tile], r = a.r, shift = 8 * r;
+    if (ai - a.a0 >= a.na) return;  // reported by k_seg_hist
     const SegArr e = a.arr[ai];
     const uint32_t run = a.rounds[ai - a.a0];
     if (!(run >> r & 1u)) return;
     const bool back = __popc(run & ((1u << r) - 1)) & 1;  // from the scratch to the planes
     const uint32_t ti = tile - e.tile0;
-    if ((uint64_t)ti * E >= e.n) {  // never when the host and device offsets agree
-        if (tid == 0) raise_error(a.err, kErrBounds);
-        return;
-    }
+    if ((uint64_t)ti * E >= e.n) return;  // reported by k_seg_hist
     const uint32_t o = ti * E, total = min((uint32_t)E, e.n - o);
     K* const pk = a.Ak + e.o0;
     K* const sk = a.Sk + (uint64_t)e.scr64 * 64;

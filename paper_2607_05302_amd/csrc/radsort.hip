@@ -1040,9 +1040,9 @@ uint32_t seg_tile(uint32_t kb, uint32_t vb, int shape)
 constexpr uint64_t kSegLargeMin = 65536;  // average array of a batch for shape 2
 
 // The tables of a group of at most `arrays` arrays and `tiles` tiles, at byte offsets from a
-// 256-byte aligned base: what k_seg_clear zeroes first (hist .. ctr), then the rest.
+// 256-byte aligned base: what k_seg_clear zeroes first (hist .. rounds), then the rest.
 struct SegTables {
-    uint64_t hist, arrived, state, ctr, zero_bytes, rounds, arr, map, total;
+    uint64_t hist, arrived, state, ctr, rounds, zero_bytes, arr, map, total;
 };
 SegTables seg_tables(uint32_t nt, uint64_t arrays, uint64_t tiles, uint64_t all_arrays,
                      uint64_t all_tiles)
@@ -1058,8 +1058,8 @@ SegTables seg_tables(uint32_t nt, uint64_t arrays, uint64_t tiles, uint64_t all_
     T.arrived = take(arrays * 4);
     T.state = take(tiles * 1024);
     T.ctr = take(4 * nt);
-    T.zero_bytes = o;
     T.rounds = take(arrays * 4);
+    T.zero_bytes = o;
     T.map = take(all_tiles * 4);
     T.arr = take(all_arrays * sizeof(SegArr));
     T.total = o;
@@ -1097,6 +1097,8 @@ void launch_seg_group(SegArgs<KB, VB> a, uint32_t tiles, hipStream_t s)
     h.map = a.map;
     h.a0 = a.a0;
     h.t0 = a.t0;
+    h.na = a.na;
+    h.group = a.group;
     h.hist = a.hist;
     h.arrived = a.arrived;
     h.rounds = a.rounds;
@@ -1142,6 +1144,7 @@ template <int KB, int VB> struct DoSegOne {
         const SegTables& T = one.T;
         const int shape = one.shape;
         SegArgs<KB, VB> a = seg_args<KB, VB>(keys, vals, sk, sv, base, T, err);
+        a.na = 1;
         const uint32_t E = seg_tile(KB, VB, shape), tiles = (n + E - 1) / E;
         // the map is all zeros too, and ends where the array's entry begins
         const uint64_t words = T.arr / 4;
@@ -1255,7 +1258,7 @@ uint64_t seg_wg_hi(const radsort_seg_tuning* t, uint64_t se)
 // Arrays of the batch that are sorted out of place in groups (kernel_seg.hpp).
 struct SegGroups {
     struct Group {
-        uint32_t a0, t0, t1;  // first array, tiles [t0, t1)
+        uint32_t a0, na, t0, t1, id;  // first array, arrays, tiles [t0, t1), number (as k_seg_plan's)
     };
     std::vector<Group> groups;
     uint32_t count = 0, tiles = 0, G64 = 0;  // arrays, tiles, group size in 64 records
@@ -1296,14 +1299,15 @@ void plan_groups(SegGroups& S, const std::vector<uint32_t>& n, uint64_t top, uin
             if (p > D64 / 2) continue;
             if (pos / S.G64 != group) {
                 group = pos / S.G64;
-                S.groups.push_back({arrays, tiles, tiles});
+                S.groups.push_back({arrays, 0, tiles, tiles, (uint32_t)group});
             }
             arrays++;
             tiles += (x + E - 1) / E;
             pos += p;
             auto& g = S.groups.back();
+            g.na++;
             g.t1 = tiles;
-            amax = std::max(amax, arrays - g.a0);
+            amax = std::max(amax, g.na);
             tmax = std::max(tmax, g.t1 - g.t0);
         }
         S.tiles = tiles;
@@ -1440,7 +1444,7 @@ template <int KB, int VB> struct DoWg {
             SegArr* arr = (SegArr*)(base + S.T.arr);
             uint32_t* map = (uint32_t*)(base + S.T.map);
             hipLaunchKernelGGL(k_seg_plan<1024>, dim3(1), dim3(1024), 0, s, offsets_dev, nseg, lo,
-                               S.hi, S.G64, E, arr, S.count);
+                               S.hi, S.G64, E, arr, S.count, map, S.tiles);
             hipLaunchKernelGGL(k_seg_map, dim3(S.count), dim3(64), 0, s, (const SegArr*)arr, E,
                                S.tiles, map);
             SegArgs<KB, VB> a =
@@ -1451,7 +1455,9 @@ template <int KB, int VB> struct DoWg {
                 hipLaunchKernelGGL(k_seg_clear, dim3(grid), dim3(256), 0, s, (uint32_t*)base, words,
                                    (SegArr*)nullptr, 0u, err);
                 a.a0 = g.a0;
+                a.na = g.na;
                 a.t0 = g.t0;
+                a.group = g.id;
                 if (S.shape == 1) launch_seg_group<KB, VB, 1>(a, g.t1 - g.t0, s);
                 else launch_seg_group<KB, VB, 2>(a, g.t1 - g.t0, s);
             }
