@@ -3,12 +3,15 @@
 // hands to an out-of-place sort (arrays smaller than T, Sec. 5).
 //
 // Workgroup i takes array i (elements [offsets[i], offsets[i+1]) of the key and payload
-// planes), or with a claim counter (zero on entry) one array after another, and sorts it if
-// it has lo < n <= E elements; with offsets null the one array of n1 elements.  The array is dealt out over all the waves, ceil(n / NT) items
-// to a lane (slot s = wave * 64 items + j * 64 + lane).  Each round is the stable counting
-// sort of Alg. 1 on 8 bits: ranks within the waves by ballots (rank_wave), digit and wave
-// starts by scans, the records to LDS at start + rank and back in slot order.  A round
-// whose digit is the same for every element is left out.
+// planes) and sorts it if it has lo < n <= E elements; with offsets null the one array of n1
+// elements.  With a claim counter (zero on entry) the workgroups claim the `step` residue
+// classes of the indices modulo `step` one after another, look at a class's arrays with one
+// lane each, and sort those of their size: an array of another size costs a lane and not a
+// claim, and neighbours of one size fall to different workgroups.  An array is dealt out over
+// all the waves, ceil(n / NT) items to a lane (slot s = wave * 64 items + j * 64 + lane).
+// Each round is the stable counting sort of Alg. 1 on 8 bits: ranks within the waves by
+// ballots (rank_wave), digit and wave starts by scans, the records to LDS at start + rank and
+// back in slot order.  A round whose digit is the same for every element is left out.
 //
 // What bounds it: the latency of a round's steps (ranks of `items` items, the barriers, two
 // scans), so a short array takes few items per lane and a small workgroup, and the payload
@@ -24,10 +27,10 @@
 
 namespace rs {
 
-template <int KB, int VB, int WAVES, int ITEMS>
+template <int KB, int VB, int WAVES, int ITEMS, bool CLAIM>
 __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4))) void k_sort_small(
     typename UInt<KB>::T* keys, typename Payload<VB>::T* vals, const uint64_t* offsets,
-    uint32_t nseg, uint64_t n1, uint32_t lo, uint32_t* err, uint32_t* claim)
+    uint32_t nseg, uint64_t n1, uint32_t lo, uint32_t* err, uint32_t* claim, uint32_t step)
 {
     using K = typename UInt<KB>::T;
     using V = typename Payload<VB>::T;
@@ -44,26 +47,38 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (!offsets && blockIdx.x == 0 && tid == 0 && err) *err = 0;  // the call's error word
 
-    // the workgroup's own array, or with a claim counter one array after another
+    // the workgroup's own array, or the arrays of one class after another
     __shared__ uint32_t claimed;
-    for (uint32_t i = blockIdx.x;; i = claimed) {
-    if (claim) {
-        __syncthreads();  // the array before is done with LDS
+    const bool many = CLAIM && step < nseg;  // classes of several arrays
+    uint32_t cls = blockIdx.x;
+    do {
+    if constexpr (CLAIM) {
+        __syncthreads();  // the class before is done
         if (tid == 0) claimed = add_agent(claim, 1u);
         __syncthreads();
-        i = claimed;
+        cls = claimed;
     }
-    if (i >= nseg) return;
+    if (cls >= step) return;
+    for (uint64_t i0 = cls; i0 < (CLAIM ? nseg : cls + 1); i0 += 64ull * step) {
+    uint64_t left = 1;  // the arrays of this size among 64 of the class, the same in every wave
+    if (many) {
+        const uint64_t i = i0 + (uint64_t)lane * step;
+        uint64_t len = 0;
+        if (i < nseg) {
+            const uint64_t first = offsets[i], end = offsets[i + 1];
+            len = end > first ? end - first : 0;
+        }
+        left = ballot(len > max(lo, 1u) && len <= (uint64_t)E);
+    }
+    for (; left; left &= left - 1) {
+    const uint64_t i = i0 + (uint64_t)__builtin_ctzll(left) * step;
     uint64_t o0 = 0, n64 = n1;
-    if (offsets) {
+    if (CLAIM || offsets) {
         o0 = offsets[i];
         const uint64_t o1 = offsets[i + 1];
         n64 = o1 > o0 ? o1 - o0 : 0;
     }
-    if (n64 <= max(lo, 1u) || n64 > (uint64_t)E) {  // nothing to do, or another's
-        if (!claim) return;
-        continue;
-    }
+    if (n64 <= max(lo, 1u) || n64 > (uint64_t)E) continue;  // nothing to do, or another's
     const uint32_t n = (uint32_t)n64;
     const int items = (int)((n + NT - 1) / NT);
     const uint32_t s0 = wave * 64 * items + lane;
@@ -93,10 +108,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
     if (diff) atomicOr((unsigned long long*)&vary, (unsigned long long)diff);
     __syncthreads();
     const uint64_t bits_vary = vary;  // bits in which the keys differ
-    if (!bits_vary) {                 // all equal: the array is sorted
-        if (!claim) return;
-        continue;
-    }
+    if (!bits_vary) continue;         // all equal: the array is sorted
     const bool wfull = ballot(nvalid != (1u << items) - 1u) == 0;
 
     for (uint32_t shift = 0; shift < 8 * KB; shift += 8) {
@@ -160,8 +172,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
             if constexpr (VB != 0) vp[s0 + j * 64] = val[j];
         }
     }
-    if (!claim) return;
     }
+    }
+    } while (CLAIM);
 }
 
 }  // namespace rs

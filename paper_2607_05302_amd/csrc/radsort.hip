@@ -1160,17 +1160,23 @@ template <int KB, int VB> struct DoSegOne {
 
 // Arrays of at most small_elems elements are sorted whole in LDS by k_sort_small, one
 // workgroup each, with no workspace.  Two shapes: 4 waves and 2048 records, of which many
-// share a compute unit, and 16 waves and the whole range.
+// share a compute unit, and 8 waves and the whole range.
 uint32_t small_elems(uint32_t kb, uint32_t vb) { return (kb + vb >= 12) ? 4096u : 8192u; }
 constexpr uint32_t kSmallShort = 2048;
+constexpr uint32_t kSmallClasses = 4096;  // claims of a batch's longer arrays at most
 
 // nseg arrays by offsets_dev, or one array of n1 elements (offsets_dev null), whose call's
 // error word is err.  Both shapes run over a batch; each array falls to one of them: a
-// workgroup per array for the short ones, workgroups that claim arrays for the `longs`
-// longer ones (claim: a zeroed counter).  A lone array above 512 elements takes the large
-// shape: its lanes hold fewer items.  4096 arrays of 2^6 .. 2^13 uint32 pairs: 45 us for the
-// short ones and 105 us for the long ones; 175 us with one shape of 8 waves that gave
-// 1024 slots to the first wave before the second got any.
+// workgroup per array for the short ones, workgroups that claim classes of arrays for the
+// longer ones, if the batch has any (longs; claim: a zeroed counter).  Up to kSmallClasses
+// arrays a class is one array; at least one workgroup per eight classes, so that many short
+// arrays are passed over quickly.  200 000 arrays of 24 to 31 uint32 pairs take 1.03 ms alone,
+// 1.08 ms with one long array among them and 145.5 ms where the workgroups, no more than the
+// long arrays, claimed the arrays one by one; 4096 arrays with 8 long ones 0.10 and 0.40 ms.
+// A lone array above 512 elements takes the large shape: its lanes hold fewer items.  4096
+// arrays of 2^6 .. 2^13 uint32 pairs: 45 us for the short ones and 105 us for the long ones;
+// 175 us with one shape of 8 waves that gave 1024 slots to the first wave before the second
+// got any.
 template <int KB, int VB> struct DoSmall {
     static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg, uint64_t n1,
                    uint32_t longs, uint32_t* err, uint32_t* claim, hipStream_t s)
@@ -1180,12 +1186,16 @@ template <int KB, int VB> struct DoSmall {
         auto* v = (typename Payload<VB>::T*)vals;
         const bool one = offsets_dev == nullptr;
         if (!one || n1 <= 512)
-            hipLaunchKernelGGL((k_sort_small<KB, VB, 4, 8>), dim3(nseg), dim3(256), 0, s, k, v,
-                               offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr);
-        if (one ? n1 > 512 : longs > 0)
-            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS>), dim3(one ? 1u : std::min(longs, 1024u)),
-                               dim3(512), 0, s, k, v, offsets_dev, nseg, n1,
-                               one ? 0u : kSmallShort, err, one ? nullptr : claim);
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 4, 8, false>), dim3(nseg), dim3(256), 0, s, k, v,
+                               offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr, nseg);
+        const uint32_t classes = std::min(nseg, kSmallClasses);
+        const uint32_t grid = std::min(classes, std::max(std::min(longs, 1024u), classes / 8));
+        if (one && n1 > 512)
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS, false>), dim3(1), dim3(512), 0, s, k,
+                               v, offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr, 1u);
+        else if (!one && longs > 0)
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS, true>), dim3(grid), dim3(512), 0, s, k,
+                               v, offsets_dev, nseg, n1, kSmallShort, err, claim, classes);
         return RADSORT_OK;
     }
 };
