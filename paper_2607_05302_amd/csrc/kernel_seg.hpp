@@ -49,9 +49,8 @@ template <int KB, int VB> struct SegArgs {
     K* Sk;                 // scratch planes
     V* Sv;
     const SegArr* arr;     // all arrays of the path
-    const uint32_t* map;   // tile -> array
+    uint32_t* map;         // tile -> array
     uint32_t a0, t0;       // first array and first tile of the group
-    uint32_t na, group;    // its arrays, its number
     uint32_t* hist;        // [array of the group][n_t][256]: counts, then element starts
     uint32_t* arrived;     // [array of the group]: tiles counted
     uint32_t* rounds;      // [array of the group]: bit r: round r runs; 0 until counted
@@ -59,6 +58,7 @@ template <int KB, int VB> struct SegArgs {
     uint32_t* ctr;         // [n_t]: tiles claimed
     uint32_t* err;
     uint32_t r;            // round
+    uint32_t na, group;    // arrays of the group, its number (k_seg_hist)
 };
 
 // The arrays of lo < n <= hi elements in order, with their scratch places and tiles: the
@@ -141,13 +141,17 @@ __global__ __launch_bounds__(NT) void k_seg_hist(SegArgs<KB, 0> a, uint32_t E)
     const uint32_t tile = a.t0 + blockIdx.x, ai = a.map[tile];
     // Only where the host's and the device's offsets disagree: the tile's array is not one of
     // the group's, or was placed in another group's scratch.  Such an array is never counted
-    // in full, so no round of it runs.
+    // in full, so no round of it runs; the tile is handed to the group's first array, past
+    // whose end the rounds find it.  (The same check in the rounds cost 1.5 us of 51.)
     const bool ours = ai - a.a0 < a.na;
     SegArr e{};
     if (ours) e = a.arr[ai];
     const uint32_t ti = tile - e.tile0, ntiles = (e.n + E - 1) / E;
     if (!ours || ti >= ntiles || e.group != a.group) {
-        if (tid == 0) raise_error(a.err, kErrBounds);
+        if (tid == 0) {
+            a.map[tile] = a.a0;
+            raise_error(a.err, kErrBounds);
+        }
         return;
     }
     const uint32_t o = ti * E, cnt = min(E, e.n - o);
@@ -235,13 +239,15 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_seg_round(SegArgs<KB, VB> a
     __syncthreads();
     const uint32_t lt = claimed, tile = a.t0 + lt;  // claimed < grid = tiles of the group
     const uint32_t ai = a.map[tile], r = a.r, shift = 8 * r;
-    if (ai - a.a0 >= a.na) return;  // reported by k_seg_hist
     const SegArr e = a.arr[ai];
     const uint32_t run = a.rounds[ai - a.a0];
     if (!(run >> r & 1u)) return;
     const bool back = __popc(run & ((1u << r) - 1)) & 1;  // from the scratch to the planes
     const uint32_t ti = tile - e.tile0;
-    if ((uint64_t)ti * E >= e.n) return;  // reported by k_seg_hist
+    if ((uint64_t)ti * E >= e.n) {  // a tile that k_seg_hist found in no array of the group
+        if (tid == 0) raise_error(a.err, kErrBounds);
+        return;
+    }
     const uint32_t o = ti * E, total = min((uint32_t)E, e.n - o);
     K* const pk = a.Ak + e.o0;
     K* const sk = a.Sk + (uint64_t)e.scr64 * 64;

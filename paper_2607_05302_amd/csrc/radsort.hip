@@ -1076,7 +1076,7 @@ SegArgs<KB, VB> seg_args(void* keys, void* vals, void* sk, void* sv, uint8_t* ba
     a.Sk = (typename UInt<KB>::T*)sk;
     a.Sv = (typename Payload<VB>::T*)sv;
     a.arr = (const SegArr*)(base + T.arr);
-    a.map = (const uint32_t*)(base + T.map);
+    a.map = (uint32_t*)(base + T.map);
     a.hist = (uint32_t*)(base + T.hist);
     a.arrived = (uint32_t*)(base + T.arrived);
     a.rounds = (uint32_t*)(base + T.rounds);

@@ -90,11 +90,13 @@ def device_run(plan, sizes, checked, rng):
             ai = at(map_, t)
             if checked and not 0 <= ai - a0 < na:
                 error = True
+                map_[t] = a0
                 continue
             n, place, tile0, group = at(arr, ai)
             ti, ntiles = (t - tile0) & 0xFFFFFFFF, -(-n // E)
             if ti >= ntiles or (checked and group != gid):
                 error = True
+                map_[t] = a0 if checked else ai
                 continue
             at(hist, ai - a0)
             arrived[ai - a0] += 1
@@ -103,16 +105,14 @@ def device_run(plan, sizes, checked, rng):
         owner = {}
         for t in range(t0, t1):  # k_seg_round
             ai = at(map_, t)
-            if checked and not 0 <= ai - a0 < na:
-                continue
             n, place, tile0, group = at(arr, ai)
+            at(hist, ai - a0)  # rounds has as many entries
             if not rounds.get(ai - a0, stale() & 1):
                 continue
             ti = (t - tile0) & 0xFFFFFFFF
             if ti * E >= n:
-                error |= not checked
+                error = True
                 continue
-            at(hist, ai - a0)
             for earlier in range(max(0, ti - 3), ti):  # look-back
                 at(state, t - t0 - (ti - earlier))
             if place * 64 + n > D64 * 64:
