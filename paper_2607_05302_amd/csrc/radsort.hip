@@ -1286,7 +1286,7 @@ void plan_groups(SegGroups& S, const std::vector<uint32_t>& n, uint64_t top, uin
                  uint32_t vb, uint64_t avail)
 {
     const uint64_t rec = kb + vb;
-    for (uint64_t D64 = avail / (64 * rec); D64 >= 128; D64 -= D64 / 16 + 1) {
+    for (uint64_t D64 = avail / (64 * rec); D64 >= 128;) {
         S.groups.clear();
         S.count = 0;
         uint64_t maxpad = 0, sum = 0;
@@ -1325,6 +1325,12 @@ void plan_groups(SegGroups& S, const std::vector<uint32_t>& n, uint64_t top, uin
         S.sk = S.T.total;
         S.sv = align_up(S.sk + D64 * 64 * kb, 256);
         if (S.sv + D64 * 64 * vb <= avail) return;
+        // the next smaller scratch, but none that the tables of all arrays and tiles alone
+        // push out (the same for as long as the same arrays take part): 2 * 10^6 arrays of
+        // 8193 keys, whose tables leave no room at all, are planned in 100 ms, not 600
+        const uint64_t fixed = S.T.total - S.T.map;
+        do D64 -= D64 / 16 + 1;
+        while (D64 >= 128 && D64 / 2 >= maxpad && fixed + D64 * 64 * rec > avail);
     }
     S.count = 0;
     S.groups.clear();
