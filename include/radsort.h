@@ -236,7 +236,8 @@ int radsort_sort_segments(void* keys, void* payload, const uint64_t* offsets,
                           const uint64_t* offsets_dev, uint32_t nseg, int key_bytes,
                           int payload_bytes, const radsort_seg_tuning* tuning,
                           const radsort_opts* opts, void* stream);
-/* Workspace of radsort_sort_segments for these arrays, or 0 on a bad argument. */
+/* Workspace of radsort_sort_segments for these arrays, or 0 on a bad argument and where
+ * host memory does not hold the plan (radsort_sort_segments: RADSORT_E_NOMEM). */
 uint64_t radsort_segments_workspace_bytes(const uint64_t* offsets, uint32_t nseg, int key_bytes,
                                           int payload_bytes, const radsort_seg_tuning* tuning,
                                           const radsort_opts* opts);

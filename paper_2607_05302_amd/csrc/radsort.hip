@@ -1356,7 +1356,7 @@ constexpr uint32_t kWgSlots = 256;
 
 int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb,
                   const radsort_seg_tuning* tuning, const radsort_opts* opts)
-{
+try {
     const uint32_t se = small_elems(kb, vb);
     P.wg_hi = seg_wg_hi(tuning, se);
     std::vector<std::pair<uint64_t, uint32_t>> big;
@@ -1413,6 +1413,8 @@ int make_seg_plan(SegPlan& P, const uint64_t* off, uint32_t nseg, int kb, int vb
     }
     P.total = o;
     return RADSORT_OK;
+} catch (const std::bad_alloc&) {  // no exception leaves a C entry point
+    return RADSORT_E_NOMEM;
 }
 
 struct LaneStreams {
