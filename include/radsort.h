@@ -121,14 +121,19 @@ typedef struct radsort_seg_tuning {
 typedef struct radsort_stats {
     uint64_t workspace_bytes;   /* extra device bytes of the last sort (peak extra memory) */
     uint64_t input_bytes;       /* n * (key_bytes + payload_bytes) of the last sort */
-    uint32_t rounds;            /* digit rounds run */
+    uint32_t rounds;            /* digit rounds of the sort (n_t): also where rounds of constant
+                                   digits were left out, or the array was sorted on chip or out
+                                   of place in the workspace */
     uint32_t error_bits;        /* device error word of the last checked call */
     /* with RADSORT_F_TIMING: milliseconds between HIP events on the call's stream */
     uint32_t timed;             /* 1 when the fields below are valid */
-    float setup_ms;             /* setup (Alg. 4) */
-    float round_ms[RADSORT_MAX_ROUNDS]; /* the sort-round kernel of each round (Alg. 5) */
+    float setup_ms;             /* setup (Alg. 4); with the count of all key positions and the
+                                   plans of all rounds where these are made at once */
+    float round_ms[RADSORT_MAX_ROUNDS]; /* the sort-round kernel of each round (Alg. 5): next to
+                                           nothing for a round left out; the whole sort in
+                                           round_ms[0] on chip or in the workspace */
     float count_ms[RADSORT_MAX_ROUNDS]; /* each round's super-tile digit counts, their scan
-                                           and the round's plan */
+                                           and the round's plan; 0 where all are made at once */
     float fixup_ms;             /* all fixup kernels (Alg. 6) and counter resets */
     float finalize_ms;          /* finalize (Alg. 7); for the baseline: a final copy-back */
     float total_ms;             /* first event to last event */

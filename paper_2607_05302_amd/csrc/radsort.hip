@@ -808,12 +808,13 @@ template <int KB, int VB> struct Ops {
         a.stbase = stcnt;
         a.stsum = st->u32(st->L.csum);
         // the ring is clear: setup or the previous round's fixup cleared it
-        g_timer.mark(kCountBegin, r, s);
-        if (!modes)
+        if (!modes) {
+            g_timer.mark(kCountBegin, r, s);
             launch_super_counts<KB, false>(g, a.Ak, a.Tk, a.pi_old, a.blen, a.f_in, a.shift, stcnt,
-                                       st->u32(st->L.csum), a.err, a.tile_ctr + 1, r,
-                                       st->plan(), s, packed);
-        g_timer.mark(kRoundBegin, r, s);
+                                           st->u32(st->L.csum), a.err, a.tile_ctr + 1, r,
+                                           st->plan(), s, packed);
+            g_timer.mark(kRoundBegin, r, s);
+        }
         int rc = launch_round_t<KB, VB, false>(g, a, s, st->dynamic, st->seq_draws);
         if (rc) return rc;
         g_timer.mark(kRoundEnd, r, s);
