@@ -554,8 +554,8 @@ __attribute__((amdgpu_waves_per_eu(SH::OCC))) void k_tile_round(TileArgs<KB, VB>
     if (a.consumed && b <= (uint32_t)E) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         for (uint32_t i = tid; i < nfills; i += NT) {
-            const uint32_t phys = pool[i];
-            if (sigma + F + i < f_in && phys < a.npi && ld_agent(a.consumed + phys) != a.tag)
+            const uint32_t phys = pool[i], h = packed ? F + i : sigma + F + i;
+            if (h >= sigma && h < f_in && phys < a.npi && ld_agent(a.consumed + phys) != a.tag)
                 raise_error(a.err, kErrOrder);
         }
     }

@@ -148,7 +148,6 @@ struct Geo {
     uint32_t oop_E = 0, oop_st_log2 = 0;  // tile and super-tile of the out-of-place round
     bool fin_temps = false;       // finalize scratch holds the two-kernel F1's temporary blocks
     bool fin_temps_pack = false;  // the same for a packed state (n_pi + sigma blocks)
-    bool pack_ok = false;         // one-call sorts pack the last round (plan_round)
     bool large_tile = false;      // the Radsort round runs LargeTile (E = 16384)
     bool tile = false;            // the Radsort round is k_tile_round
     bool tile_large = false;      // ... with its large tile
@@ -295,10 +294,6 @@ int make_geo(Geo& g, uint64_t n, int key_bytes, int payload_bytes, int digit_bit
     // the packed last round: its finalize is F1 over n_pi + sigma blocks, then the
     // spare blocks' slots copied into place (no compaction)
     g.fin_temps_pack = shared || !fin_coop(g.npi + g.sigma, g.b, g.kb + g.vb, cus).covers;
-    g.pack_ok = true;
-#ifdef RS_DEBUG_ORDER
-    g.pack_ok = false;  // the ordering check follows the rounds of the paper
-#endif
     return RADSORT_OK;
 }
 
@@ -309,7 +304,7 @@ uint64_t finalize_bytes(const Geo& g, bool pack)
                              pack ? g.fin_temps_pack : g.fin_temps);
 }
 
-// pack: the workspace of a sort whose last round is packed (Geo::pack_ok): sigma
+// pack: the workspace of a sort whose last round is packed (one-call sorts): sigma
 // extra blocks, and the block permutations and finalize arrays over n_pi + sigma
 // blocks.  The small arrays come first, so that the error word's place depends
 // on n_t and sigma only.
@@ -1393,7 +1388,7 @@ try {
         Geo g;
         int rc = make_geo(g, n, kb, vb, (int)c.bits, &o);
         if (rc) return rc;
-        P.lane_bytes[l] = std::max(P.lane_bytes[l], make_layout(g, false, g.pack_ok).total);
+        P.lane_bytes[l] = std::max(P.lane_bytes[l], make_layout(g, false, true).total);
         P.large.push_back(i);
         P.lane.push_back(l);
         P.choice.push_back(c);
@@ -1602,8 +1597,8 @@ static int state_create(radsort_state** out, void* keys, void* payload, uint64_t
     radsort_state* st = new (std::nothrow) radsort_state();
     if (!st) return RADSORT_E_NOMEM;
     st->g = g;
-    st->pack = pack && g.pack_ok;
-    st->L = make_layout(g, false, st->pack);
+    st->pack = pack;
+    st->L = make_layout(g, false, pack);
     st->keys = keys;
     st->vals = payload;
     st->count = n;
@@ -1777,7 +1772,7 @@ uint64_t radsort_workspace_bytes(uint64_t n, int key_bytes, int payload_bytes, i
 {
     Geo g;
     if (make_geo(g, n, key_bytes, payload_bytes, digit_bits, opts)) return 0;
-    return make_layout(g, false, g.pack_ok).total;
+    return make_layout(g, false, true).total;
 }
 
 uint64_t radsort_oop_workspace_bytes(uint64_t n, int key_bytes, int payload_bytes,
@@ -1819,7 +1814,7 @@ int radsort_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes, int
     rc = make_geo(g, n, key_bytes, payload_bytes, digit_bits, opts);
     if (rc) return rc;
     if (n <= 1) return RADSORT_OK;
-    if (sort_is_small(g, opts)) return sort_small(keys, payload, g, make_layout(g, false, g.pack_ok), opts, (hipStream_t)stream);
+    if (sort_is_small(g, opts)) return sort_small(keys, payload, g, make_layout(g, false, true), opts, (hipStream_t)stream);
     radsort_state* st = nullptr;
     rc = state_create(&st, keys, payload, n, key_bytes, payload_bytes, digit_bits, opts, true);
     if (rc) return rc;
@@ -2205,7 +2200,7 @@ int radsort_sort_pairs_noalloc(void* keys, void* payload, uint64_t n, int key_by
     rc = make_geo(g, n, key_bytes, payload_bytes, digit_bits, &o);
     if (rc) return rc;
     if (n <= 1) return RADSORT_OK;
-    const Layout L = make_layout(g, false, g.pack_ok);
+    const Layout L = make_layout(g, false, true);
     if (L.total > (uint64_t)RADSORT_NOALLOC_SCRATCH_BYTES) return RADSORT_E_NOMEM;
     void* ws = nullptr;
     rc = scratch_address(&ws);
@@ -2224,7 +2219,7 @@ int radsort_sort_pairs_noalloc(void* keys, void* payload, uint64_t n, int key_by
     st.vals = payload;
     st.count = n;
     st.seq_draws = flags & RADSORT_F_SEQ_DRAWS;
-    st.pack = g.pack_ok;
+    st.pack = true;
     // the launch forms that query no occupancy (the query's cache allocates)
     st.dynamic = true;
     st.shared = true;
