@@ -34,19 +34,18 @@ def table_path(key_bytes: int, payload_bytes: int) -> str:
     return os.path.join(HERE, "tuning", f"segments_k{key_bytes}_v{payload_bytes}.json")
 
 
-_tables = {}  # path -> (what the file was, its classes); read again when the file changes
+_tables = {}  # path -> (the file's bytes, its classes): parsed again when the bytes differ
 
 
 def load_table(key_bytes: int, payload_bytes: int):
     """[(max_log2n, b, digit_bits), ...] from the tuning file, or None."""
     path = table_path(key_bytes, payload_bytes)
     try:
-        st = os.stat(path)
-        stamp = (st.st_mtime_ns, st.st_size, st.st_ino)
+        with open(path, "rb") as f:
+            text = f.read()
         known = _tables.get(path)
-        if known is None or known[0] != stamp:
-            with open(path) as f:
-                known = (stamp, tuple(tuple(c) for c in json.load(f)["classes"]))
+        if known is None or known[0] != text:
+            known = (text, tuple(tuple(c) for c in json.loads(text)["classes"]))
             _tables[path] = known
     except (OSError, ValueError):
         return None
