@@ -43,9 +43,9 @@ __device__ __forceinline__ void pin(uint32_t& x) { asm volatile("" : "+v"(x)); }
 // slot order (item j of all lanes before item j + 1), two 16-bit ranks per word of rp
 // (0xFFFF: no element; nvalid bit j: item j of this lane holds one; wfull: all of them
 // do).  myh: the wave's digit counts, zero on entry, complete on return; myor: its OR
-// table, zero on entry (OR only).  items: the items looked at; the rest are empty and their
-// words of rp left as they are.
-template <int FB, bool OR, typename K, int ITEMS>
+// table, zero on entry (OR only).  items: the items looked at, a multiple of G; the rest are
+// empty and their words of rp left as they are.
+template <int FB, bool OR, int G = 1, typename K, int ITEMS>
 __device__ __forceinline__ void rank_wave(const K (&key)[ITEMS], uint32_t nvalid, bool wfull,
                                           uint32_t shift, uint32_t bits, uint16_t* myh,
                                           uint64_t* myor, uint32_t (&rp)[ITEMS / 2],
@@ -88,7 +88,7 @@ __device__ __forceinline__ void rank_wave(const K (&key)[ITEMS], uint32_t nvalid
 #pragma unroll
         for (int j = 0; j < ITEMS; j++) {
             if (j < from) continue;
-            if (j >= items) break;
+            if (j % G == 0 && j >= items) break;
             if constexpr (ITEMS >= 32) __builtin_amdgcn_sched_barrier(0);  // registers
             const uint32_t dw = (uint32_t)(key[j] >> shift);
             uint32_t r = 0xFFFFu;
@@ -118,7 +118,7 @@ __device__ __forceinline__ void rank_wave(const K (&key)[ITEMS], uint32_t nvalid
             const uint64_t mybit = 1ull << lane;
 #pragma unroll
             for (int j = 1; j < ITEMS; j++) {
-                if (j >= items) break;
+                if (j % G == 0 && j >= items) break;
                 if constexpr (ITEMS >= 32) __builtin_amdgcn_sched_barrier(0);  // registers
                 const uint32_t dg = (uint32_t)(key[j] >> shift) & dmask;
                 __hip_atomic_fetch_or(myor + dg, mybit, __ATOMIC_RELAXED,

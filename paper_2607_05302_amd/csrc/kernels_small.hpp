@@ -9,17 +9,21 @@
 // lane each, and sort those of their size: an array of another size costs a lane and not a
 // claim, and neighbours of one size fall to different workgroups.  An array is dealt out over
 // all the waves, ceil(n / NT) items to a lane (slot s = wave * 64 items + j * 64 + lane).
-// Each round is the stable counting sort of Alg. 1 on 8 bits: ranks within the waves by
-// ballots (rank_wave), digit and wave starts by scans, the records to LDS at start + rank and
-// back in slot order.  A round whose digit is the same for every element is left out.
+// Each round is the stable counting sort of Alg. 1 on 8 bits: ranks within the waves by the OR
+// table or by ballots (rank_wave), digit and wave starts by scans, the records to LDS at start
+// + rank and back in slot order.  A round whose digit is the same for every element is left out.
 //
 // What bounds it: the latency of a round's steps (ranks of `items` items, the barriers, two
-// scans), so a short array takes few items per lane and a small workgroup, and the payload
-// is staged in the keys' bytes after them, which lets four workgroups of the large shape
-// share a compute unit.  16384 arrays of 1911 .. 2048 uint32 pairs: 752 us with one shape of
-// 8192 slots, 319 us with the short one; 4096 arrays of 7643 .. 8192 pairs 372 and 363 us;
-// one array of 1500 pairs 290 us through the general path, 36 us here (the copy of the
-// input and the wait for the stream included).
+// scans) and, with many arrays, the instructions of the ranks.  So a short array takes few
+// items per lane and a small workgroup; the large shape takes its items G at a time, without a
+// branch between them, so that their LDS accesses are in flight together (a branch per item
+// also held 128 registers, two workgroups to a compute unit; 84 now), and ranks by the OR table
+// unless the keys are 8 bytes without payload, whose registers it would need.  The payload is
+// staged in the keys' bytes after them.  Per batch, with a branch per item and ballots / now:
+// 20 000 uint32 pairs arrays of 8192 records 1602 / 1372 us, of 3000 877 / 812 us; of 4096
+// records of 16 bytes 1757 / 1559 us; G = 4, 2 there 1504, 1479 us by ballots; one array of
+// 1500 pairs 37.1 / 35.6 us (the copy of the input and the wait for the stream included;
+// 290 us through the general path).
 #pragma once
 
 #include "common.hpp"
@@ -37,6 +41,9 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
     constexpr int NT = WAVES * 64, E = NT * ITEMS, SMAX = 256, DW = SMAX / 64;
     static_assert(NT >= SMAX, "one digit per thread");
     static_assert(E <= 32768, "16-bit positions");
+    constexpr bool OR_RANK = WAVES == 8 && !(KB == 8 && VB == 0);
+    constexpr int G = WAVES == 8 ? ITEMS / 4 : 1;  // items taken together
+    static_assert(!OR_RANK || sizeof(K) * E >= WAVES * SMAX * 8, "OR tables live in the stage");
     // the keys in sorted order, then the payload in the same bytes
     __shared__ __align__(16) unsigned char stage[E * (KB > VB ? KB : VB)];
     K* const lk = (K*)stage;
@@ -80,7 +87,7 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
     }
     if (n64 <= max(lo, 1u) || n64 > (uint64_t)E) continue;  // nothing to do, or another's
     const uint32_t n = (uint32_t)n64;
-    const int items = (int)((n + NT - 1) / NT);
+    const int items = (int)((n + NT * G - 1) / (NT * G)) * G;
     const uint32_t s0 = wave * 64 * items + lane;
     K* const kp = keys + o0;
     V* vp = nullptr;
@@ -110,15 +117,35 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
     const uint64_t bits_vary = vary;  // bits in which the keys differ
     if (!bits_vary) continue;         // all equal: the array is sorted
     const bool wfull = ballot(nvalid != (1u << items) - 1u) == 0;
+    // f of every item the lane holds, G without a branch in a wave whose items are all there
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int j0 = 0; j0 < ITEMS; j0 += G) {
+            if (j0 >= items) break;
+            if (wfull) {
+#pragma unroll
+                for (int j = j0; j < j0 + G; j++) f(j);
+            } else {
+#pragma unroll
+                for (int j = j0; j < j0 + G; j++)
+                    if (nvalid >> j & 1u) f(j);
+            }
+        }
+    };
 
     for (uint32_t shift = 0; shift < 8 * KB; shift += 8) {
         if (!(bits_vary >> shift & 0xFFu)) continue;
         uint16_t* const myh = wh + wave * SMAX;
+        uint64_t* const myor = (uint64_t*)stage + wave * SMAX;
+        if constexpr (OR_RANK) {
+            __syncthreads();  // the stage was read
+            for (uint32_t i = lane; i < SMAX; i += 64) myor[i] = 0;
+        }
         for (uint32_t i = lane; i < SMAX / 2; i += 64) ((uint32_t*)myh)[i] = 0;
         uint32_t rp[ITEMS / 2];
 #pragma unroll
         for (int j = 0; j < ITEMS / 2; j++) rp[j] = ~0u;
-        rank_wave<8, false>(key, nvalid, wfull, shift, 8, myh, nullptr, rp, items);
+        rank_wave<8, OR_RANK, G>(key, nvalid, wfull, shift, 8, myh, myor, rp, items);
         __syncthreads();
         uint32_t c = 0;
         if (tid < SMAX) {
@@ -140,38 +167,26 @@ __global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(4)))
             for (int w = 0; w < WAVES; w++) wh[w * SMAX + tid] += (uint16_t)ex;
         }
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++) {
-            if (nvalid >> j & 1u) {
-                uint32_t p = j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu;
-                p += myh[(uint32_t)(key[j] >> shift) & 0xFFu];
-                lk[p] = key[j];
-                if constexpr (VB != 0)
-                    rp[j / 2] = j & 1 ? (rp[j / 2] & 0xFFFFu) | p << 16 : (rp[j / 2] & 0xFFFF0000u) | p;
-            }
-        }
+        each([&](int j) {
+            uint32_t p = j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu;
+            p += myh[(uint32_t)(key[j] >> shift) & 0xFFu];
+            lk[p] = key[j];
+            if constexpr (VB != 0)
+                rp[j / 2] = j & 1 ? (rp[j / 2] & 0xFFFFu) | p << 16 : (rp[j / 2] & 0xFFFF0000u) | p;
+        });
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < ITEMS; j++)
-            if (nvalid >> j & 1u) key[j] = lk[s0 + j * 64];
+        each([&](int j) { key[j] = lk[s0 + j * 64]; });
         if constexpr (VB != 0) {
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++)
-                if (nvalid >> j & 1u) lv[j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu] = val[j];
+            each([&](int j) { lv[j & 1 ? rp[j / 2] >> 16 : rp[j / 2] & 0xFFFFu] = val[j]; });
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < ITEMS; j++)
-                if (nvalid >> j & 1u) val[j] = lv[s0 + j * 64];
+            each([&](int j) { val[j] = lv[s0 + j * 64]; });
         }
     }
-#pragma unroll
-    for (int j = 0; j < ITEMS; j++) {
-        if (nvalid >> j & 1u) {
-            kp[s0 + j * 64] = key[j];
-            if constexpr (VB != 0) vp[s0 + j * 64] = val[j];
-        }
-    }
+    each([&](int j) {
+        kp[s0 + j * 64] = key[j];
+        if constexpr (VB != 0) vp[s0 + j * 64] = val[j];
+    });
     }
     }
     } while (CLAIM);

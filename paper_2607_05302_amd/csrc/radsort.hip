@@ -1162,34 +1162,35 @@ constexpr uint32_t kSmallShort = 2048;
 constexpr uint32_t kSmallClasses = 4096;  // claims of a batch's longer arrays at most
 
 // nseg arrays by offsets_dev, or one array of n1 elements (offsets_dev null), whose call's
-// error word is err.  Both shapes run over a batch; each array falls to one of them: a
-// workgroup per array for the short ones, workgroups that claim classes of arrays for the
-// longer ones, if the batch has any (longs; claim: a zeroed counter).  Up to kSmallClasses
-// arrays a class is one array; at least one workgroup per eight classes, so that many short
-// arrays are passed over quickly.  200 000 arrays of 24 to 31 uint32 pairs take 1.03 ms alone,
-// 1.08 ms with one long array among them and 145.5 ms where the workgroups, no more than the
-// long arrays, claimed the arrays one by one; 4096 arrays with 8 long ones 0.10 and 0.40 ms.
-// A lone array above 512 elements takes the large shape: its lanes hold fewer items.  4096
-// arrays of 2^6 .. 2^13 uint32 pairs: 45 us for the short ones and 105 us for the long ones;
-// 175 us with one shape of 8 waves that gave 1024 slots to the first wave before the second
-// got any.
+// error word is err.  Where most arrays of a batch are longer ones, the large shape takes all
+// of them, a workgroup per array: 3000 arrays, three of four of 6000 uint32 pairs and one of
+// 1000, take 203 us so and 224 us with a launch of each shape.  Else each array falls to one
+// of the two: a workgroup per array for the short ones, workgroups that claim classes of arrays
+// for the longer ones (claim: a zeroed counter).  Up to kSmallClasses arrays a class is one
+// array; at least one workgroup per eight classes, so that many short arrays are passed over
+// quickly.  200 000 arrays of 24 to 31 uint32 pairs take 1.03 ms alone, 1.08 ms with one long
+// array among them and 145.5 ms where the workgroups, no more than the long arrays, claimed the
+// arrays one by one; 4096 arrays with 8 long ones 0.10 and 0.40 ms.  A lone array above 512
+// elements takes the large shape: its lanes hold fewer items.  4096 arrays of 2^6 .. 2^13
+// uint32 pairs: 151 us, and 177 us with the large shape alone.
 template <int KB, int VB> struct DoSmall {
     static int run(void* keys, void* vals, const uint64_t* offsets_dev, uint32_t nseg, uint64_t n1,
-                   uint32_t longs, uint32_t* err, uint32_t* claim, hipStream_t s)
+                   uint32_t shorts, uint32_t longs, uint32_t* err, uint32_t* claim, hipStream_t s)
     {
         constexpr int ITEMS = KB + VB >= 12 ? 8 : 16;
         auto* k = (typename UInt<KB>::T*)keys;
         auto* v = (typename Payload<VB>::T*)vals;
         const bool one = offsets_dev == nullptr;
-        if (!one || n1 <= 512)
+        const bool all = !one && longs >= shorts && longs > nseg / 2;  // the large shape alone
+        if (one ? n1 <= 512 : shorts > 0 && !all)
             hipLaunchKernelGGL((k_sort_small<KB, VB, 4, 8, false>), dim3(nseg), dim3(256), 0, s, k, v,
                                offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr, nseg);
         const uint32_t classes = std::min(nseg, kSmallClasses);
         const uint32_t grid = std::min(classes, std::max(std::min(longs, 1024u), classes / 8));
-        if (one && n1 > 512)
-            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS, false>), dim3(1), dim3(512), 0, s, k,
-                               v, offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr, 1u);
-        else if (!one && longs > 0)
+        if (one ? n1 > 512 : all)
+            hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS, false>), dim3(nseg), dim3(512), 0, s,
+                               k, v, offsets_dev, nseg, n1, 0u, err, (uint32_t*)nullptr, nseg);
+        else if (longs > 0)
             hipLaunchKernelGGL((k_sort_small<KB, VB, 8, ITEMS, true>), dim3(grid), dim3(512), 0, s, k,
                                v, offsets_dev, nseg, n1, kSmallShort, err, claim, classes);
         return RADSORT_OK;
@@ -1342,8 +1343,7 @@ struct SegPlan {
     uint32_t wg_count = 0, wg_slots = 0;  // arrays of the one-workgroup path, workgroups
     uint64_t wg_off = 0, wg_slot_bytes = 0, wg_list_off = 0;
     uint64_t total = 0;
-    bool any_small = false;   // arrays of k_sort_small
-    uint32_t small_long = 0;  // ... of its large shape
+    uint32_t small_short = 0, small_long = 0;  // arrays of k_sort_small's two shapes
 };
 
 // Workgroups of the one-workgroup path (each with its own T); they never wait
@@ -1362,8 +1362,7 @@ try {
         const uint64_t n = off[i + 1] - off[i];
         if (n <= 1) continue;
         if (n <= se) {
-            P.any_small = true;
-            P.small_long += n > kSmallShort;
+            (n > kSmallShort ? P.small_long : P.small_short)++;
             continue;
         }
         if (n <= P.wg_hi) {
@@ -1568,7 +1567,7 @@ static int sort_small(void* keys, void* payload, const Geo& g, const Layout& L,
     const bool timing = opts && (opts->flags & RADSORT_F_TIMING);
     if (timing) g_timer.begin();
     g_timer.mark(kStart, 0, s);
-    int rc = dispatch<DoSmall>(g.kb, g.vb, keys, payload, (const uint64_t*)nullptr, 1u, g.n, 0u, err,
+    int rc = dispatch<DoSmall>(g.kb, g.vb, keys, payload, (const uint64_t*)nullptr, 1u, g.n, 0u, 0u, err,
                                (uint32_t*)nullptr, s);
     g_timer.mark(kRoundEnd, 0, s);
     g_timer.end();
@@ -2042,9 +2041,9 @@ int radsort_sort_segments(void* keys, void* payload, const uint64_t* offsets,
                          L->s[l]);
         }
     }
-    if (!rc && P.any_small) {
+    if (!rc && (P.small_short || P.small_long)) {
         rc = dispatch<DoSmall>(key_bytes, payload_bytes, keys, payload, offsets_dev, nseg,
-                               (uint64_t)0, P.small_long, err_small, err_small + 3 + kSegLanes, s);
+                               (uint64_t)0, P.small_short, P.small_long, err_small, err_small + 3 + kSegLanes, s);
     }
     if (!rc && P.wg_count) {
         rc = dispatch<DoWg>(key_bytes, payload_bytes, keys, payload, offsets_dev, nseg, P, ws,
