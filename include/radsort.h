@@ -84,7 +84,7 @@ extern "C" {
                                        holding input of the round checks the mark; a
                                        missing mark sets error bit 4 (radsort_stats) and
                                        the call returns RADSORT_E_ORDER.  Needs b <= the
-                                       round's tile (8192 elements for 4-byte keys);
+                                       round's tile (4096 elements or more);
                                        slower; for tests.  With RADSORT_F_DEBUG_PLANT as
                                        well the marks carry a wrong tag, so that every
                                        checked draw reports (a test of the check) */
@@ -105,11 +105,12 @@ typedef struct radsort_opts {
  * that run the Radsort steps on streams: an array of n elements takes the first class
  * c with ceil(log2 n) <= max_log2n[c].  Arrays above 4 423 680 elements always run
  * there; a smaller array (but above the whole-in-LDS limit of 8192, or 4096 for
- * records of 12 bytes or more) runs there when its class has block_elems > 0, and on
- * one workgroup of the batched kernel when block_elems = 0 or no class covers it.
- * digit_bits must be 4, 8 or 11 and block_elems 0 or a power of two in [64, 65536];
- * a class with block_elems = 0 takes the batched kernel's own digits (5 bits, b =
- * 1024) and its digit_bits is not used. */
+ * records of 12 bytes or more) runs there when its class has block_elems > 0, and in
+ * the batch's own scratch (see radsort_sort_segments) when block_elems = 0 or no class
+ * covers it.  digit_bits must be 4, 8 or 11 and block_elems 0 or a power of two in
+ * [64, 65536]; a class with block_elems = 0 takes the digits of the batched kernels (8
+ * bits out of place, 5 bits and b = 1024 on one workgroup) and its digit_bits is not
+ * used. */
 #define RADSORT_SEG_CLASSES 32
 typedef struct radsort_seg_tuning {
     uint32_t classes;
@@ -143,12 +144,18 @@ typedef struct radsort_stats {
  * radsort_sort_pairs -- sort keys[0..n) in place, ascending and stable, moving
  * payload[i] with keys[i].  Radsort, the driver of Alg. 2: setup (Alg. 4), then
  * for t = n_t-1 .. 0 a sort phase (Alg. 5) and a fixup phase (Alg. 6), then
- * finalize (Alg. 7).  Each round first counts the digits of its own input (the
- * histogram loop of Alg. 1, per group of tiles) and takes its bucket starts and
- * the P and f it leaves from those counts by closed forms.  The last round is
+ * finalize (Alg. 7).  With digits of at most 8 bits, b >= 1024 and the default draw
+ * order, one pass counts the digits of all key positions and plans all rounds (bucket
+ * starts, P and f by closed forms); rounds whose digit is the same for every element
+ * are left out.  Otherwise each round first counts the digits of its own input (the
+ * histogram loop of Alg. 1, per group of tiles).  The last round is
  * packed (see radsort_workspace_bytes): every element lands at the slot of its
  * final position, so that finalize permutes whole blocks and merges at most one
  * partial block per bucket, with no compaction; the result is the same.
+ * Two kinds of small arrays are not sorted by Radsort, with the same result: those of
+ * at most 8192 elements (4096 for records of 12 bytes or more) are sorted on chip by
+ * one workgroup; those whose records fit the workspace once more (T and the extra
+ * blocks, about 3 sigma b records) are sorted out of place in it (Alg. 1, 8-bit digits).
  *   key_bytes      4 or 8 (uint32 / uint64 keys; signed or float keys are not
  *                  handled: the order is that of the unsigned bit patterns)
  *   payload_bytes  0 (payload must be NULL), 4 or 8
@@ -199,7 +206,9 @@ uint64_t radsort_workspace_bytes(uint64_t n, int key_bytes, int payload_bytes,
  * radsort_oop_sort_pairs -- the out-of-place LSD radix sort of Alg. 1 on the
  * same tile code: n_t rounds, each a stable counting sort from one array into a
  * second one of n elements, ping-ponging between the caller's arrays and
- * workspace buffers.  Same arguments, result and ownership as
+ * workspace buffers.  Below 2^26 elements, where its tables fit the workspace, with
+ * 8-bit digits whatever digit_bits is and without the rounds of constant digits; arrays
+ * of at most 8192 (4096) elements on chip.  Same arguments, result and ownership as
  * radsort_sort_pairs; it needs n (key_bytes + payload_bytes) extra bytes plus the
  * digit count and look-back state: radsort_oop_workspace_bytes().
  */

@@ -117,8 +117,8 @@ struct TileArgs {
     // the input blocks in logical order, which keeps every draw behind the blocks
     // already read although the offsets make buckets draw up to sigma blocks early.
     const uint32_t* pack_est;
-    const uint32_t* mode;    // this round's mode, decided on the device (RoundModes), or null:
-                             // packed when pack_est is given
+    const uint32_t* mode;    // this round's mode, decided on the device (kModeRun, kModeSkip or
+                             // kModePacked), or null: packed when pack_est is given
     K* Xk;
     V* Xv;
     uint32_t npi_x;          // physical blocks a draw can name: npi, + sigma when packed

@@ -1222,10 +1222,11 @@ int read_err(radsort_state* st, hipStream_t s, uint32_t* bits)
 
 // ---- many arrays at once ---------------------------------------------------------
 
-// Arrays of at most kSmallE<KB, VB> elements are sorted whole in LDS by
-// k_sort_small (one workgroup each, no workspace).  Arrays up to wg_max_elems()
-// are sorted by k_radsort_wg, one workgroup per array, all of them in one
-// launch, each workgroup with its own T.  Larger ones run the Radsort steps in
+// Arrays of at most small_elems() elements are sorted whole in LDS by k_sort_small (one
+// workgroup each, no workspace).  Arrays up to wg_max_elems() share the scratch of up to
+// kWgSlots workgroups in the workspace: those that fit half of it are sorted out of place
+// there, group by group (kernel_seg.hpp), the others by k_radsort_wg, one workgroup per
+// array, each with its part of the scratch as its T.  Larger ones run the Radsort steps in
 // the dynamic launch form, spread over kSegLanes streams forked from the caller's
 // stream, each lane with its own workspace.
 constexpr uint32_t kSegLanes = 4;
@@ -1535,7 +1536,8 @@ static bool sort_is_small(const Geo& g, const radsort_opts* opts)
     return g.n <= small_elems(g.kb, g.vb);
 }
 // A one-call sort whose array fits its own workspace once more (T and the extra blocks hold
-// 3 sigma b records) runs out of place there: five launches instead of twenty.
+// 3 sigma b records) runs out of place there: 2 launches and one per key byte (6 of 4-byte
+// keys) instead of some twenty.
 static SegOne sort_in_workspace_plan(const radsort_state* st)
 {
     const Geo& g = st->g;

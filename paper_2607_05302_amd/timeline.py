@@ -10,10 +10,12 @@ tiles, in microseconds).  Steps (stamp pairs):
     load+rank  the tile's loads issued, stable ranks within waves, loads waited for
     counts     tile counts published, digit scan, wave offsets
     stage      records staged in LDS in (digit, slot) order
-    lookback   digit starts from the super-tile start and earlier tiles' counts
+    lookback   digit starts from all earlier tiles (one-call sorts), or from the
+               super-tile start and its earlier tiles
     (the default draw order stages the tile after publishing its draws)
     d:count    blocks drawn and written per digit, F, their scans
-    d:pool+wait  pool entries read, waits for the tiles that read those blocks
+    d:pool+wait  pool entries read (and waits for the tiles that read those blocks,
+               where the look-back does not cover all tiles)
     d:publish  the tile's draws published in pi'
     d:first    each digit's first block (drawn by an earlier tile) waited for
     ptrs       the table of block addresses
