@@ -206,7 +206,8 @@ uint64_t radsort_workspace_bytes(uint64_t n, int key_bytes, int payload_bytes,
  * radsort_oop_sort_pairs -- the out-of-place LSD radix sort of Alg. 1 on the
  * same tile code: n_t rounds, each a stable counting sort from one array into a
  * second one of n elements, ping-ponging between the caller's arrays and
- * workspace buffers.  Below 2^26 elements, where its tables fit the workspace, with
+ * workspace buffers.  Below 2^26 elements (2^24 with
+ * RADSORT_F_SHARED), where its tables fit the workspace, with
  * 8-bit digits whatever digit_bits is and without the rounds of constant digits; arrays
  * of at most 8192 (4096) elements on chip.  Same arguments, result and ownership as
  * radsort_sort_pairs; it needs n (key_bytes + payload_bytes) extra bytes plus the

@@ -572,19 +572,26 @@ void launch_super_counts(const Geo& g, const typename UInt<KB>::T* Ak,
 }
 
 // The claimed forms (no co-residency needed): one workgroup per tile, or for the
-// claim loop at most as many workgroups as fit at once.
+// claim loop at most as many workgroups as fit at once.  `lds`, for a claim loop beside other
+// work: bytes of LDS that keep its workgroups to one per compute unit, those of other sorts
+// included.  Two of them to a unit (the records of 12 bytes fit so since the loop needs 127
+// registers) get in each other's way: 8 out-of-place sorts at once of 2^24 .. 2^24.5, 2^24.5 ..
+// 2^26 and 2^26 .. 2^27 records (uint32 and uint64 keys, uint32 payload) sort 10.6, 13.0 and
+// 15.5 G keys/s with what fits, 13.7, 14.8 and 16.6 with one per unit of each sort, 15.0, 16.1
+// and 17.5 with one per unit of all.
 template <typename Args>
 int launch_dynamic(const void* kern, uint32_t tiles, uint32_t threads, Args& a, hipStream_t s,
-                   bool loop)
+                   bool loop, uint32_t lds = 0)
 {
     uint32_t grid = tiles;
     if (loop) {
         const int cap = resident_capacity(kern, threads);
         if (cap <= 0) return RADSORT_E_DEVICE;
-        grid = std::min<uint32_t>(tiles, (uint32_t)cap);
+        grid = std::min<uint32_t>(tiles, lds ? std::min<uint32_t>((uint32_t)cap, device_cus())
+                                             : (uint32_t)cap);
     }
     void* args[] = {(void*)&a};
-    RS_HIP(hipLaunchKernel(kern, dim3(grid), dim3(threads), args, 0, s));
+    RS_HIP(hipLaunchKernel(kern, dim3(grid), dim3(threads), args, lds, s));
     return RADSORT_OK;
 }
 
@@ -596,7 +603,7 @@ int launch_dynamic(const void* kern, uint32_t tiles, uint32_t threads, Args& a, 
 // always draw in the sequential order.  The out-of-place round draws nothing.
 template <int KB, int VB, bool OOP>
 int launch_round_t(const Geo& g, TileArgs<KB, VB>& a, hipStream_t s, bool dyn = false,
-                   bool seq = true)
+                   bool seq = true, bool shared = false)
 {
     using N = TileCfg<KB, VB, false, OOP>;
     using Wd = TileCfg<KB, VB, true, OOP>;
@@ -650,7 +657,9 @@ int launch_round_t(const Geo& g, TileArgs<KB, VB>& a, hipStream_t s, bool dyn = 
         else
             kern = g.bits == 8 ? (const void*)&k_round<KB, VB, OOP, 8, 256, NS, M, true>
                                : (const void*)&k_round<KB, VB, OOP, 0, 256, NS, M, true>;
-        if (g.bits <= 8) return launch_dynamic(kern, tiles, nt, a, s, OOP);
+        // the loop's own LDS is 50 to 90 KB of a compute unit's 160: 32 more keep a second out
+        if (g.bits <= 8)
+            return launch_dynamic(kern, tiles, nt, a, s, OOP, OOP && shared ? 32u << 10 : 0u);
         return launch_dynamic(
             (const void*)&k_round<KB, VB, OOP, 0, 2048, typename Wd::Shape, M, !OOP>, tiles,
             64 * Wd::WAVES, a, s, OOP);
@@ -912,7 +921,7 @@ template <int KB, int VB> struct Ops {
 
     // Alg. 1 rounds, ping-ponging between the caller's arrays and the workspace
     static int oop_sort(void* keys, void* vals, const Geo& g, const Layout& L, uint8_t* ws,
-                        bool dyn, hipStream_t s)
+                        bool dyn, bool shared, hipStream_t s)
     {
         // each round's element starts come from its own digit counts
         PlanPtrs p{(uint32_t*)(ws + L.S), (uint32_t*)(ws + L.Pidx), (uint32_t*)(ws + L.Plen),
@@ -950,7 +959,7 @@ template <int KB, int VB> struct Ops {
                                           a.shift, stcnt, (uint32_t*)(ws + L.csum), a.err,
                                           a.tile_ctr + 1, r, p, s, false);
             g_timer.mark(kRoundBegin, r, s);
-            int rc = launch_round_t<KB, VB, true>(g, a, s, dyn);
+            int rc = launch_round_t<KB, VB, true>(g, a, s, dyn, true, shared);
             if (rc) return rc;
             g_timer.mark(kRoundEnd, r, s);
         }
@@ -1011,9 +1020,9 @@ template <int KB, int VB> struct DoLogical {
 };
 template <int KB, int VB> struct DoOop {
     static int run(void* k, void* v, const Geo& g, const Layout& L, uint8_t* ws, bool dyn,
-                   hipStream_t s)
+                   bool shared, hipStream_t s)
     {
-        return Ops<KB, VB>::oop_sort(k, v, g, L, ws, dyn, s);
+        return Ops<KB, VB>::oop_sort(k, v, g, L, ws, dyn, shared, s);
     }
 };
 
@@ -1110,14 +1119,20 @@ void launch_seg_group(SegArgs<KB, VB> a, uint32_t tiles, hipStream_t s)
 // 2^15, 47 / 55 / 78 at 2^16, - / 64 / 83 at 2^18, - / 103 / 112 at 2^21, - / 147 / 136 at 2^22, - / 394 /
 // 348 at 2^24; uint64 + uint32 77 / 81 / 110 at 2^15, 88 / 87 / 114 at 2^16, 222 / 173 / 174 at 2^20,
 // 344 / 244 / 207 at 2^21.
+//
+// Beside other work on the GPU the look-back over all tiles of a long array loses more than it
+// saves: 8 sorts at once of 2^24.5 .. 2^26 records (uint32 and uint64 keys, uint32 payload)
+// sort 11.6 G keys/s so and 16.1 by the rounds with counting passes (launch_dynamic); of 2^23
+// .. 2^24 records 24.7 and 13.2, of 2^20 .. 2^23 26.4 and 8.0 G keys/s.
 struct SegOne {
     int shape = -1;
     SegTables T{};
 };
-SegOne seg_one(const Geo& g, uint64_t avail)
+constexpr uint64_t kSegSharedEnd = 1ull << 24;  // a shared GPU: arrays below this
+SegOne seg_one(const Geo& g, uint64_t avail, bool shared)
 {
     SegOne one;
-    if (g.n >= 1ull << kSegValueBits) return one;
+    if (g.n >= (shared ? kSegSharedEnd : 1ull << kSegValueBits)) return one;
     const bool wide = g.kb + g.vb >= 12 || g.kb == 8;
     int shape = g.n <= (wide ? 1u << 16 : 1u << 18) ? 0 : g.n < (wide ? 1u << 20 : 1u << 22) ? 1 : 2;
     for (; shape <= 2; shape++) {
@@ -1543,7 +1558,7 @@ static SegOne sort_in_workspace_plan(const radsort_state* st)
     const Geo& g = st->g;
     const uint64_t room = st->L.total - st->L.Tk, records = g.n * (g.kb + g.vb) + 256;
     if (st->debug_order || records > room) return SegOne{};
-    return seg_one(g, room - records);
+    return seg_one(g, room - records, st->shared);
 }
 static int sort_in_workspace(radsort_state* st, const SegOne& one, hipStream_t s)
 {
@@ -1883,15 +1898,16 @@ int radsort_oop_sort_pairs(void* keys, void* payload, uint64_t n, int key_bytes,
     // the out-of-place round runs faster in the form without co-residency (one
     // workgroup per tile) at every size and block tried, so it always takes it
     const bool dyn = true;
-    const SegOne one = seg_one(g, L.total - L.ring);
-    if (one.shape >= 0) {  // otherwise more tiles than look-back words
+    const bool shared = opts && (opts->flags & RADSORT_F_SHARED);
+    const SegOne one = seg_one(g, L.total - L.ring, shared);
+    if (one.shape >= 0) {
         g_timer.mark(kStart, 0, s);
         rc = dispatch<DoSegOne>(g.kb, g.vb, keys, payload, (uint32_t)n, (void*)(ws + L.alt_k),
                                 (void*)(ws + L.alt_v), ws + L.ring, (uint32_t*)(ws + L.ctr) + g.nt,
                                 one, s);
         g_timer.mark(kRoundEnd, 0, s);
     } else {
-        rc = dispatch<DoOop>(g.kb, g.vb, keys, payload, g, L, ws, dyn, s);
+        rc = dispatch<DoOop>(g.kb, g.vb, keys, payload, g, L, ws, dyn, shared, s);
     }
     g_timer.end();
     g_stats.timed = 0;
